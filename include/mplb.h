@@ -280,19 +280,24 @@ int mplb_poke(mplb_t* h, int set, int i, long node, double value);
 int mplb_poison(mplb_t* h);
 
 /* Test hook: the tile height of this lattice's step.  0 (default) lets
- * mplb_step choose: 16 rows for the coupled step with FP32 populations on a
+ * mplb_step choose: on a small lattice (one whose step reads and writes less
+ * than about 285 MB, with further limits for FP64 and 16-bit populations, and
+ * no study switch set) a kernel of three-dimensional bricks, one thread per
+ * node; otherwise a march along z, with 16 rows for the coupled step with FP32 populations on a
  * lattice that fills 512 such blocks, and for the CHE-only step in FP32
  * compute (any storage) the kernel in which a thread owns two nodes of a
  * 128 x 8 tile on a lattice of at least 5 million nodes that fills at least
  * 384 of those; 8 otherwise.
- * 8 or 16 forces one (16 where it exists, else MPLB_E_INVAL).  The tiling
- * changes which work a block does, not the arithmetic of a node, so the
- * fields are bitwise the same; mplb_step_many always uses 8 rows. */
+ * 8 or 16 forces that march (16 where it exists, else MPLB_E_INVAL).  The
+ * kernel and the tiling change which work a block does, not the arithmetic of
+ * a node, so the fields are bitwise the same; mplb_step_many uses 8 rows, or
+ * bricks for a batch that is small as a whole. */
 int mplb_force_tile_rows(mplb_t* h, int rows);
 
-/* The kernel and work split that mplb_step uses for a lattice of nx*ny*nz
- * nodes in this precision and mode, with `rows` as for mplb_force_tile_rows
- * (0: the automatic choice).  A host computation: it needs no device and no
+/* The marching kernel and work split for a lattice of nx*ny*nz nodes in this
+ * precision and mode, with `rows` as for mplb_force_tile_rows (0: the
+ * automatic choice among the marches; the bricks that mplb_step takes on small
+ * lattices instead have no such split and are not reported).  A host computation: it needs no device and no
  * lattice.  out[0]: 0 the coupled step on 64 x 8 tiles, 1 on 64 x 16 tiles,
  * 2 the CHE-only step with one node per thread (64 x 8 tiles), 3 with two
  * nodes per thread (128 x 8 tiles); out[1], out[2]: tile width and height in

@@ -1,7 +1,9 @@
 // Device building blocks of the libmplb kernels: lattice tables, storage
 // access, pull streaming with bounce-back, the finite differences of
-// Eqs. 35-36, the macroscopic closure (Eqs. 29-30) and the two moment-space
-// collisions.  Included by the kernel translation units.
+// Eqs. 35-36, the macroscopic closure (Eqs. 29-30), the two moment-space
+// collisions, and the parts that the step kernels share (block order, axis
+// wrapping, buffer resources, the same differences on planes held in LDS).
+// Included by the kernel translation units.
 #pragma once
 
 #include <cmath>
@@ -593,5 +595,101 @@ __device__ inline bool all_finite(const T* v, int k) {
   return s == 0;  // NaN or Inf times 0 is NaN
 }
 
+// ------------------------------------------------- parts of the step kernels
+// Block -> logical tile with a contiguous run of tiles per XCD (workgroups
+// are dispatched round-robin over the 8 XCDs).
+__device__ inline int logical_block(int b, int nb) {
+  const int X = 8;
+  int per = nb / X, rem = nb % X;
+  int xcd = b % X, k = b / X;
+  return (xcd < rem) ? xcd * (per + 1) + k : rem * (per + 1) + (xcd - rem) * per + k;
+}
+
+// periodic wrap, or clamp onto the wall layer (mirror ghost of phi)
+__device__ inline int map_axis(int v, int n, int wall) {
+  if (wall) return v < 0 ? 0 : (v >= n ? n - 1 : v);
+  v %= n;
+  return v < 0 ? v + n : v;
+}
+__device__ inline int clamp_axis(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
+__device__ inline int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_at(const void* base) {
+  // no stride, full 32-bit range, untyped 32-bit data (gfx9 descriptor word 3)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, -1, 0x00020000);
+}
+
+// Eq. 36 at a ring position c of the middle plane pc, with the planes below
+// (pm) and above (pp); 2/3 per face and 1/12 per corner (s7: the D3Q7
+// weights, 1 per face).
+template <class T, int PX>
+__device__ inline T lap_lds(const T* pm, const T* pc, const T* pp, int c, bool s7 = false) {
+  T c0 = pc[c];
+  if (s7)
+    return (((pc[c + 1] - c0) + (pc[c - 1] - c0)) + ((pc[c + PX] - c0) + (pc[c - PX] - c0))) +
+           ((pp[c] - c0) + (pm[c] - c0));
+  T lf = ((pc[c - 1] - c0) + (pc[c + 1] - c0)) + ((pc[c - PX] - c0) + (pc[c + PX] - c0)) + ((pm[c] - c0) + (pp[c] - c0));
+  T lc = ((pm[c - PX - 1] - c0) + (pm[c - PX + 1] - c0)) + ((pm[c + PX - 1] - c0) + (pm[c + PX + 1] - c0)) +
+         ((pp[c - PX - 1] - c0) + (pp[c - PX + 1] - c0)) + ((pp[c + PX - 1] - c0) + (pp[c + PX + 1] - c0));
+  return (T)(2.0 / 3.0) * lf + (T)(1.0 / 12.0) * lc;
+}
+
+// Eq. 35: face neighbours weigh 1/3, corners 1/24 (s7: central differences).
+template <class T, int PX>
+__device__ inline void grad_lds(const T* pm, const T* pc, const T* pp, int c, T gr[3], bool s7 = false) {
+  if (s7) {
+    gr[0] = (T)0.5 * (pc[c + 1] - pc[c - 1]);
+    gr[1] = (T)0.5 * (pc[c + PX] - pc[c - PX]);
+    gr[2] = (T)0.5 * (pp[c] - pm[c]);
+    return;
+  }
+  T a = pm[c + PX + 1], b = pm[c + PX - 1], d = pm[c - PX + 1], e = pm[c - PX - 1];
+  T A = pp[c + PX + 1], Bv = pp[c + PX - 1], D = pp[c - PX + 1], E = pp[c - PX - 1];
+  T cx = ((a - b) + (d - e)) + ((A - Bv) + (D - E));
+  T cy = ((a - d) + (b - e)) + ((A - D) + (Bv - E));
+  T cz = ((A - a) + (Bv - b)) + ((D - d) + (E - e));
+  gr[0] = (T)(1.0 / 3.0) * (pc[c + 1] - pc[c - 1]) + (T)(1.0 / 24.0) * cx;
+  gr[1] = (T)(1.0 / 3.0) * (pc[c + PX] - pc[c - PX]) + (T)(1.0 / 24.0) * cy;
+  gr[2] = (T)(1.0 / 3.0) * (pp[c] - pm[c]) + (T)(1.0 / 24.0) * cz;
+}
+
+// Test hook (Coef::poison): fill shared memory with all-ones words, NaN in
+// every storage type, so that a read of a slot no stage has written shows in
+// the results.  Callers follow it with a barrier.
+__device__ inline void poison_shared(void* p, int bytes) {
+  uint32_t* w = (uint32_t*)p;
+  for (int i = threadIdx.x; i < bytes / 4; i += blockDim.x) w[i] = 0xffffffffu;
+}
+
+// at least 4 waves per SIMD for FP32 compute (<= 128 VGPRs), 2 for FP64
+template <int P>
+constexpr int waves_per_eu() { return P == MPLB_F64 ? 2 : 4; }
+
+// Study variants of a step kernel, compile-time so that the default kernels
+// carry no code for them: D3Q7 finite differences (Eqs. 35-36), and Gamma T
+// of Eq. 28 in place of the printed Eq. 32.  Built for FP64 and FP32 storage.
+constexpr int kVarS7 = 1, kVarF28 = 2;
+// S^g = 1 off the stress moments (the host sets it from the rates; any
+// precision): the D3Q15 collision forms only the stress moments of g
+constexpr int kVarUnit = 4;
+
 }  // namespace dev
+
+// the coefficients in the compute type
+template <class T>
+inline Coef<T> cast_coef(const Coef<double>& c) {
+  Coef<T> o;
+  o.rho_l = (T)c.rho_l; o.rho_g = (T)c.rho_g; o.drho = (T)c.drho;
+  o.beta = (T)c.beta; o.kappa = (T)c.kappa; o.eta = (T)c.eta; o.A = (T)c.A; o.mob = (T)c.mob;
+  o.rho_ref = (T)c.rho_ref;
+  for (int a = 0; a < 3; ++a) o.grav[a] = (T)c.grav[a];
+  for (int i = 0; i < 7; ++i) o.sf[i] = (T)c.sf[i];
+  for (int i = 0; i < 15; ++i) o.lg[i] = (T)c.lg[i];
+  o.vel_kind = c.vel_kind; o.velU = (T)c.velU; o.vel_ct = (T)c.vel_ct; o.vel_ct_prev = (T)c.vel_ct_prev;
+  o.stencil7 = c.stencil7; o.forcing28 = c.forcing28;
+  o.unit_rates = c.unit_rates;
+  o.poison = c.poison;
+  return o;
+}
+
 }  // namespace mplb

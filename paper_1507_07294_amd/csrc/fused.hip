@@ -45,24 +45,6 @@ using namespace dev;
 
 constexpr int kTX = 64;
 
-// Block -> logical tile with a contiguous run of tiles per XCD (workgroups
-// are dispatched round-robin over the 8 XCDs).
-__device__ inline int logical_block(int b, int nb) {
-  const int X = 8;
-  int per = nb / X, rem = nb % X;
-  int xcd = b % X, k = b / X;
-  return (xcd < rem) ? xcd * (per + 1) + k : rem * (per + 1) + (xcd - rem) * per + k;
-}
-
-// periodic wrap, or clamp onto the wall layer (mirror ghost of phi)
-__device__ inline int map_axis(int v, int n, int wall) {
-  if (wall) return v < 0 ? 0 : (v >= n ? n - 1 : v);
-  v %= n;
-  return v < 0 ? v + n : v;
-}
-__device__ inline int clamp_axis(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
-__device__ inline int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-
 // Source offsets of one lattice column (x, y): for a velocity component c in
 // {-1, 0, 1}, xs[c+1] is the source x (x - c, wrapped) and xb[c+1] says the
 // population comes through an x wall; ys holds y * nx likewise.
@@ -131,10 +113,6 @@ __device__ inline int source(const Column& c, const Plane& p, int cx, int cy, in
 template <class S>
 __device__ inline const S* plane_base(const void* arr0, size_t arr, int pitch, int zoff) {
   return (const S*)arr0 + (arr * (size_t)pitch + (size_t)zoff);
-}
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_at(const void* base) {
-  // no stride, full 32-bit range, untyped 32-bit data (gfx9 descriptor word 3)
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, -1, 0x00020000);
 }
 // NTL: non-temporal load (cache-policy bit 1), for data that no other block
 // reads again.
@@ -269,48 +247,6 @@ __device__ inline void pull_gq(const Geo& G, const void* gb, const Column& c, co
   g[0] = (T)raw[0];
 #pragma unroll
   for (int i = PACK ? 7 : 1; i < Q; ++i) g[i] = (T)raw[i];
-}
-
-// Eq. 36 at a ring position c of the middle plane pc, with the planes below
-// (pm) and above (pp); 2/3 per face and 1/12 per corner (s7: the D3Q7
-// weights, 1 per face).
-template <class T, int PX>
-__device__ inline T lap_lds(const T* pm, const T* pc, const T* pp, int c, bool s7 = false) {
-  T c0 = pc[c];
-  if (s7)
-    return (((pc[c + 1] - c0) + (pc[c - 1] - c0)) + ((pc[c + PX] - c0) + (pc[c - PX] - c0))) +
-           ((pp[c] - c0) + (pm[c] - c0));
-  T lf = ((pc[c - 1] - c0) + (pc[c + 1] - c0)) + ((pc[c - PX] - c0) + (pc[c + PX] - c0)) + ((pm[c] - c0) + (pp[c] - c0));
-  T lc = ((pm[c - PX - 1] - c0) + (pm[c - PX + 1] - c0)) + ((pm[c + PX - 1] - c0) + (pm[c + PX + 1] - c0)) +
-         ((pp[c - PX - 1] - c0) + (pp[c - PX + 1] - c0)) + ((pp[c + PX - 1] - c0) + (pp[c + PX + 1] - c0));
-  return (T)(2.0 / 3.0) * lf + (T)(1.0 / 12.0) * lc;
-}
-
-// Eq. 35: face neighbours weigh 1/3, corners 1/24 (s7: central differences).
-template <class T, int PX>
-__device__ inline void grad_lds(const T* pm, const T* pc, const T* pp, int c, T gr[3], bool s7 = false) {
-  if (s7) {
-    gr[0] = (T)0.5 * (pc[c + 1] - pc[c - 1]);
-    gr[1] = (T)0.5 * (pc[c + PX] - pc[c - PX]);
-    gr[2] = (T)0.5 * (pp[c] - pm[c]);
-    return;
-  }
-  T a = pm[c + PX + 1], b = pm[c + PX - 1], d = pm[c - PX + 1], e = pm[c - PX - 1];
-  T A = pp[c + PX + 1], Bv = pp[c + PX - 1], D = pp[c - PX + 1], E = pp[c - PX - 1];
-  T cx = ((a - b) + (d - e)) + ((A - Bv) + (D - E));
-  T cy = ((a - d) + (b - e)) + ((A - D) + (Bv - E));
-  T cz = ((A - a) + (Bv - b)) + ((D - d) + (E - e));
-  gr[0] = (T)(1.0 / 3.0) * (pc[c + 1] - pc[c - 1]) + (T)(1.0 / 24.0) * cx;
-  gr[1] = (T)(1.0 / 3.0) * (pc[c + PX] - pc[c - PX]) + (T)(1.0 / 24.0) * cy;
-  gr[2] = (T)(1.0 / 3.0) * (pp[c] - pm[c]) + (T)(1.0 / 24.0) * cz;
-}
-
-// Test hook (Coef::poison): fill shared memory with all-ones words, NaN in
-// every storage type, so that a read of a slot no stage has written shows in
-// the results.  Callers follow it with a barrier.
-__device__ inline void poison_shared(void* p, int bytes) {
-  uint32_t* w = (uint32_t*)p;
-  for (int i = threadIdx.x; i < bytes / 4; i += blockDim.x) w[i] = 0xffffffffu;
 }
 
 template <int P, int TY, int HALO>
@@ -459,18 +395,6 @@ struct MuMaker {
     }
   }
 };
-
-// at least 4 waves per SIMD for FP32 compute (<= 128 VGPRs), 2 for FP64
-template <int P>
-constexpr int waves_per_eu() { return P == MPLB_F64 ? 2 : 4; }
-
-// Study variants of a step kernel, compile-time so that the default kernels
-// carry no code for them: D3Q7 finite differences (Eqs. 35-36), and Gamma T
-// of Eq. 28 in place of the printed Eq. 32.  Built for FP64 and FP32 storage.
-constexpr int kVarS7 = 1, kVarF28 = 2;
-// S^g = 1 off the stress moments (the host sets it from the rates; any
-// precision): the D3Q15 collision forms only the stress moments of g
-constexpr int kVarUnit = 4;
 
 // The coupled step of logical block lb of one lattice (NT: streaming stores;
 // Q: velocities of the NSE lattice, 15 or 19; V: variant bits, the study
@@ -949,22 +873,6 @@ k_fused_che2(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur, Tiling TL) {
   plane(z1 - 1, std::false_type{});
 }
 
-template <class T>
-Coef<T> cast_coef_f(const Coef<double>& c) {
-  Coef<T> o;
-  o.rho_l = (T)c.rho_l; o.rho_g = (T)c.rho_g; o.drho = (T)c.drho;
-  o.beta = (T)c.beta; o.kappa = (T)c.kappa; o.eta = (T)c.eta; o.A = (T)c.A; o.mob = (T)c.mob;
-  o.rho_ref = (T)c.rho_ref;
-  for (int a = 0; a < 3; ++a) o.grav[a] = (T)c.grav[a];
-  for (int i = 0; i < 7; ++i) o.sf[i] = (T)c.sf[i];
-  for (int i = 0; i < 15; ++i) o.lg[i] = (T)c.lg[i];
-  o.vel_kind = c.vel_kind; o.velU = (T)c.velU; o.vel_ct = (T)c.vel_ct; o.vel_ct_prev = (T)c.vel_ct_prev;
-  o.stencil7 = c.stencil7; o.forcing28 = c.forcing28;
-  o.unit_rates = c.unit_rates;
-  o.poison = c.poison;
-  return o;
-}
-
 // Rows per tile: 8 (512 threads, two blocks per CU) except for the coupled
 // step with FP32 populations on a large lattice, which takes 16 (1024
 // threads, one block per CU).
@@ -1181,61 +1089,48 @@ template <int P>
 hipError_t fused_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs& B, int cur, hipStream_t s,
                       int rows) {
   using T = typename Prec<P>::T;
-  Coef<T> C = cast_coef_f<T>(Cd);
+  Coef<T> C = cast_coef<T>(Cd);
   if (G.wall_x || G.wall_y) return fused_impl2<P, true>(mode, G, C, B, cur, s, rows);
   return fused_impl2<P, false>(mode, G, C, B, cur, s, rows);
 }
 
-template <int P, bool XYWALL, bool NT, int V>
-hipError_t many_impl2(const void* dtab, int count, int total_blocks, int flip, hipStream_t s) {
-  using T = typename Prec<P>::T;
-  hipLaunchKernelGGL((k_fused_many<P, kTY, XYWALL, NT, V>), dim3((unsigned)total_blocks), dim3(kTX * kTY), 0, s,
-                     (const BatchItem<T>*)dtab, count, flip);
-  return hipGetLastError();
+// The batched marching kernel of a form.
+template <int P, bool XYWALL, bool NT>
+const void* many_kernel2(bool unit) {
+  return unit ? (const void*)k_fused_many<P, kTY, XYWALL, NT, kVarUnit>
+              : (const void*)k_fused_many<P, kTY, XYWALL, NT, 0>;
 }
-
-// nsteps batched steps as a chain of kernel nodes (flip alternating), built
-// directly rather than by stream capture so that it works on any stream.
-template <int P, bool XYWALL, bool NT, int V>
-hipError_t many_graph2(const void* dtab, int count, int total_blocks, int nsteps, hipGraph_t* out) {
-  hipGraph_t g = nullptr;
-  hipError_t e = hipGraphCreate(&g, 0);
-  if (e != hipSuccess) return e;
-  hipGraphNode_t prev = nullptr;
-  for (int k = 0; k < nsteps && e == hipSuccess; ++k) {
-    int flip = k & 1;
-    const void* tab = dtab;
-    void* args[] = {(void*)&tab, (void*)&count, (void*)&flip};
-    hipKernelNodeParams kp{};
-    kp.func = (void*)k_fused_many<P, kTY, XYWALL, NT, V>;
-    kp.gridDim = dim3((unsigned)total_blocks);
-    kp.blockDim = dim3(kTX * kTY);
-    kp.sharedMemBytes = 0;
-    kp.kernelParams = args;
-    kp.extra = nullptr;
-    hipGraphNode_t node = nullptr;
-    e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
-    prev = node;
+template <int P>
+const void* many_kernel1(const BatchForm& f) {
+  if (f.wall) return f.nt ? many_kernel2<P, true, true>(f.unit) : many_kernel2<P, true, false>(f.unit);
+  return f.nt ? many_kernel2<P, false, true>(f.unit) : many_kernel2<P, false, false>(f.unit);
+}
+const void* many_kernel(int P, const BatchForm& f) {
+  if (f.bricks != kBricksNone) return brick_many_kernel(P, f.wall, f.unit, f.bricks);
+  switch (P) {
+    case MPLB_F64: return many_kernel1<MPLB_F64>(f);
+    case MPLB_F32: return many_kernel1<MPLB_F32>(f);
+    case MPLB_F32_F16: return many_kernel1<MPLB_F32_F16>(f);
+    case MPLB_F32_BF16: return many_kernel1<MPLB_F32_BF16>(f);
+    default: return nullptr;
   }
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(g);
-    return e;
-  }
-  *out = g;
-  return hipSuccess;
+}
+unsigned many_threads(Bricks br) {
+  return br == kBricksNone ? kTX * kTY : (br == kBricksWide ? kBrickThreadsWide : kBrickThreadsNarrow);
 }
 
 template <int P>
-int batch_fill_impl(void* table, int i, const Geo& G, const Coef<double>& Cd, const Bufs& B, int cur0, int block0) {
+int batch_fill_impl(void* table, int i, const Geo& G, const Coef<double>& Cd, const Bufs& B, int cur0, int block0,
+                    Bricks br) {
   using T = typename Prec<P>::T;
   BatchItem<T> it{};
   it.G = G;
   it.TL = make_tiling(G, kTY, 16);
   it.B = B;
-  it.C = cast_coef_f<T>(Cd);
+  it.C = cast_coef<T>(Cd);
   it.cur0 = cur0;
   it.block0 = block0;
-  it.nblocks = it.TL.tiles_x * it.TL.tiles_y * it.TL.nseg;
+  it.nblocks = br == kBricksNone ? it.TL.tiles_x * it.TL.tiles_y * it.TL.nseg : brick_blocks(G, br);
   ((BatchItem<T>*)table)[i] = it;
   return it.nblocks;
 }
@@ -1271,6 +1166,8 @@ size_t noalloc_table_bytes() { return kNoAllocTableBytes; }
 
 hipError_t launch_fused_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                              hipStream_t s, int rows) {
+  const Bricks br = rows == 0 ? step_bricks(P, mode, G, C) : kBricksNone;
+  if (br != kBricksNone) return launch_brick_step(P, mode, G, C, B, cur, br, s);
   switch (P) {
     case MPLB_F64: return fused_impl<MPLB_F64>(mode, G, C, B, cur, s, rows);
     case MPLB_F32: return fused_impl<MPLB_F32>(mode, G, C, B, cur, s, rows);
@@ -1285,60 +1182,54 @@ size_t fused_batch_item_bytes(int P) {
 }
 
 int fused_batch_fill(int P, void* table, int i, const Geo& G, const Coef<double>& C, const Bufs& B, int cur0,
-                     int block0) {
+                     int block0, Bricks br) {
   switch (P) {
-    case MPLB_F64: return batch_fill_impl<MPLB_F64>(table, i, G, C, B, cur0, block0);
-    case MPLB_F32: return batch_fill_impl<MPLB_F32>(table, i, G, C, B, cur0, block0);
-    case MPLB_F32_F16: return batch_fill_impl<MPLB_F32_F16>(table, i, G, C, B, cur0, block0);
-    case MPLB_F32_BF16: return batch_fill_impl<MPLB_F32_BF16>(table, i, G, C, B, cur0, block0);
+    case MPLB_F64: return batch_fill_impl<MPLB_F64>(table, i, G, C, B, cur0, block0, br);
+    case MPLB_F32: return batch_fill_impl<MPLB_F32>(table, i, G, C, B, cur0, block0, br);
+    case MPLB_F32_F16: return batch_fill_impl<MPLB_F32_F16>(table, i, G, C, B, cur0, block0, br);
+    case MPLB_F32_BF16: return batch_fill_impl<MPLB_F32_BF16>(table, i, G, C, B, cur0, block0, br);
     default: return -1;
   }
 }
 
-hipError_t launch_fused_many(int P, bool xywall, bool nt, bool unit, const void* dtab, int count, int total_blocks,
-                             int flip, hipStream_t s) {
-#define MPLB_MANY_V(PP, W, N)                                                                        \
-  return unit ? many_impl2<PP, W, N, kVarUnit>(dtab, count, total_blocks, flip, s)                  \
-              : many_impl2<PP, W, N, 0>(dtab, count, total_blocks, flip, s);
-#define MPLB_MANY(PP)                                                                                \
-  if (xywall) {                                                                                      \
-    if (nt) MPLB_MANY_V(PP, true, true)                                                              \
-    MPLB_MANY_V(PP, true, false)                                                                     \
-  }                                                                                                  \
-  if (nt) MPLB_MANY_V(PP, false, true)                                                               \
-  MPLB_MANY_V(PP, false, false)
-  switch (P) {
-    case MPLB_F64: MPLB_MANY(MPLB_F64)
-    case MPLB_F32: MPLB_MANY(MPLB_F32)
-    case MPLB_F32_F16: MPLB_MANY(MPLB_F32_F16)
-    case MPLB_F32_BF16: MPLB_MANY(MPLB_F32_BF16)
-    default: return hipErrorInvalidValue;
-  }
-#undef MPLB_MANY
-#undef MPLB_MANY_V
+hipError_t launch_fused_many(int P, const BatchForm& form, const void* dtab, int count, int total_blocks, int flip,
+                             hipStream_t s) {
+  const void* k = many_kernel(P, form);
+  if (!k) return hipErrorInvalidValue;
+  void* args[] = {(void*)&dtab, (void*)&count, (void*)&flip};
+  return hipLaunchKernel(k, dim3((unsigned)total_blocks), dim3(many_threads(form.bricks)), args, 0, s);
 }
 
-hipError_t build_fused_many_graph(int P, bool xywall, bool nt, bool unit, const void* dtab, int count,
-                                  int total_blocks, int nsteps, hipGraph_t* out) {
-#define MPLB_GRAPH_V(PP, W, N)                                                                       \
-  return unit ? many_graph2<PP, W, N, kVarUnit>(dtab, count, total_blocks, nsteps, out)             \
-              : many_graph2<PP, W, N, 0>(dtab, count, total_blocks, nsteps, out);
-#define MPLB_GRAPH(PP)                                                                               \
-  if (xywall) {                                                                                      \
-    if (nt) MPLB_GRAPH_V(PP, true, true)                                                             \
-    MPLB_GRAPH_V(PP, true, false)                                                                    \
-  }                                                                                                  \
-  if (nt) MPLB_GRAPH_V(PP, false, true)                                                              \
-  MPLB_GRAPH_V(PP, false, false)
-  switch (P) {
-    case MPLB_F64: MPLB_GRAPH(MPLB_F64)
-    case MPLB_F32: MPLB_GRAPH(MPLB_F32)
-    case MPLB_F32_F16: MPLB_GRAPH(MPLB_F32_F16)
-    case MPLB_F32_BF16: MPLB_GRAPH(MPLB_F32_BF16)
-    default: return hipErrorInvalidValue;
+// nsteps batched steps as a chain of kernel nodes (flip alternating), built
+// directly rather than by stream capture so that it works on any stream.
+hipError_t build_fused_many_graph(int P, const BatchForm& form, const void* dtab, int count, int total_blocks,
+                                  int nsteps, hipGraph_t* out) {
+  const void* k = many_kernel(P, form);
+  if (!k) return hipErrorInvalidValue;
+  hipGraph_t g = nullptr;
+  hipError_t e = hipGraphCreate(&g, 0);
+  if (e != hipSuccess) return e;
+  hipGraphNode_t prev = nullptr;
+  for (int step = 0; step < nsteps && e == hipSuccess; ++step) {
+    int flip = step & 1;
+    void* args[] = {(void*)&dtab, (void*)&count, (void*)&flip};
+    hipKernelNodeParams kp{};
+    kp.func = const_cast<void*>(k);
+    kp.gridDim = dim3((unsigned)total_blocks);
+    kp.blockDim = dim3(many_threads(form.bricks));
+    kp.sharedMemBytes = 0;
+    kp.kernelParams = args;
+    kp.extra = nullptr;
+    hipGraphNode_t node = nullptr;
+    e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
+    prev = node;
   }
-#undef MPLB_GRAPH
-#undef MPLB_GRAPH_V
+  if (e != hipSuccess) {
+    (void)hipGraphDestroy(g);
+    return e;
+  }
+  *out = g;
+  return hipSuccess;
 }
 
 size_t fused_stream_threshold() { return kStreamBytes; }

@@ -7,8 +7,9 @@
 // wall (half-way bounce-back).  Arrays are structure-of-arrays, one array per
 // population, `pitch` elements apart.
 //
-// The time step itself is one kernel (fused.hip).  This file holds the
-// per-node kernels around it:
+// The time step itself is one kernel: a march (fused.hip) or, for small
+// lattices, three-dimensional bricks (brick.h, compiled here).  This file holds
+// the per-node kernels around it:
 //   k_phi, k_mu   phi = sum_i f_i (Eq. 13) and mu (Eqs. 2, 36) into arrays,
 //                 for read-out, totals and the initial state
 //   k_macro       one macroscopic field at the current level
@@ -20,6 +21,7 @@
 #include "common.h"
 #include "device.h"
 #include "launch.h"
+#include "brick.h"
 
 namespace mplb {
 namespace {
@@ -374,22 +376,6 @@ __global__ void k_poke(Geo G, Bufs B, int cur, int set, int i, int n, double v) 
   using L = Lat<P, packed_q<P, COUPLED, Q>()>;
   if (set == 0) L::stf(B.f[cur], G.pitch, i, n, (T)v);
   else L::stg(B.f[cur], B.g[cur], G.pitch, i, n, (T)v);
-}
-
-template <class T>
-Coef<T> cast_coef(const Coef<double>& c) {
-  Coef<T> o;
-  o.rho_l = (T)c.rho_l; o.rho_g = (T)c.rho_g; o.drho = (T)c.drho;
-  o.beta = (T)c.beta; o.kappa = (T)c.kappa; o.eta = (T)c.eta; o.A = (T)c.A; o.mob = (T)c.mob;
-  o.rho_ref = (T)c.rho_ref;
-  for (int a = 0; a < 3; ++a) o.grav[a] = (T)c.grav[a];
-  for (int i = 0; i < 7; ++i) o.sf[i] = (T)c.sf[i];
-  for (int i = 0; i < 15; ++i) o.lg[i] = (T)c.lg[i];
-  o.vel_kind = c.vel_kind; o.velU = (T)c.velU; o.vel_ct = (T)c.vel_ct; o.vel_ct_prev = (T)c.vel_ct_prev;
-  o.stencil7 = c.stencil7; o.forcing28 = c.forcing28;
-  o.unit_rates = c.unit_rates;
-  o.poison = c.poison;
-  return o;
 }
 
 inline dim3 grid_for(int N) { return dim3((unsigned)((N + kBlock - 1) / kBlock)); }

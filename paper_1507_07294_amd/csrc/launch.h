@@ -13,28 +13,50 @@ hipError_t launch_phi(int P, int mode, const Geo& G, const Bufs& B, int cur, hip
 hipError_t launch_mu(int P, const Geo& G, const Coef<double>& C, const Bufs& B, hipStream_t s);
 // one step as a single z-marching kernel (fused.hip): reads buffer `cur`,
 // writes buffer 1 - cur.  rows: tile height of the coupled step, 0 for the
-// automatic choice, 8 or 16 to force one (16: FP32 populations only)
+// automatic choice (bricks for small lattices), 8 or 16 to force a march (16:
+// FP32 populations only)
 hipError_t launch_fused_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                              hipStream_t s, int rows = 0);
-// the kernel and work split launch_fused_step uses (host computation only;
-// rows as there, assumed valid for P and mode)
+// The same step in three-dimensional bricks, one thread per node (brick.hip),
+// for the lattices that step_bricks picks.
+enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksWide = 2 };
+Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C);
+hipError_t launch_brick_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, Bricks br,
+                             hipStream_t s);
+int brick_blocks(const Geo& G, Bricks br);
+// the same for a batch of D3Q15 lattices: `bytes` and `nodes` over the batch,
+// `padded` the nodes that bricks of either width cover (index Bricks)
+Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[3]);
+const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br);
+constexpr int kBrickThreadsNarrow = 256, kBrickThreadsWide = 512;
+// the kernel and work split of a marching step (host computation only; rows as
+// for launch_fused_step, assumed valid for P and mode)
 Shape launch_shape(int P, int mode, const Geo& G, int rows);
 // Batched coupled step over a device table of BatchItem<T> (T of P):
 // fused_batch_item_bytes gives the item size, fused_batch_fill writes item i
 // of a host table and returns that lattice's block count, launch_fused_many
-// runs one step of every item (buffer parity cur0 ^ flip).
+// runs one step of every item (buffer parity cur0 ^ flip).  BatchForm: the
+// kernel of the batch, which all of its items share.
 size_t fused_batch_item_bytes(int P);
 int fused_batch_fill(int P, void* table, int i, const Geo& G, const Coef<double>& C, const Bufs& B, int cur0,
-                     int block0);
-// (nt: streaming stores, for batches whose step moves more than
-// kStreamBytes; see fused_step_bytes; unit: every item has S^g = 1 off the
-// stress moments, the form its lattice uses alone)
-hipError_t launch_fused_many(int P, bool xywall, bool nt, bool unit, const void* dtab, int count, int total_blocks,
-                             int flip, hipStream_t s);
+                     int block0, Bricks br);
+// bricks: kBricksNone for the march; wall: some lattice has a wall on the x or
+// y axis (bricks: on any axis); nt: streaming stores (march), for batches whose
+// step moves more than kStreamBytes, see fused_step_bytes; unit: every item has
+// S^g = 1 off the stress moments, the form its lattice uses alone
+struct BatchForm {
+  Bricks bricks;
+  bool wall, nt, unit;
+  bool operator==(const BatchForm& o) const {
+    return bricks == o.bricks && wall == o.wall && nt == o.nt && unit == o.unit;
+  }
+};
+hipError_t launch_fused_many(int P, const BatchForm& form, const void* dtab, int count, int total_blocks, int flip,
+                             hipStream_t s);
 // the same for nsteps steps (flip = k & 1 at step k) as a graph of kernel
 // nodes; the caller instantiates, launches and destroys it
-hipError_t build_fused_many_graph(int P, bool xywall, bool nt, bool unit, const void* dtab, int count,
-                                  int total_blocks, int nsteps, hipGraph_t* out);
+hipError_t build_fused_many_graph(int P, const BatchForm& form, const void* dtab, int count, int total_blocks,
+                                  int nsteps, hipGraph_t* out);
 // Device address of the static batch table of mplb_step_many_noalloc on
 // device `dev` (the current device), looked up on the first call for that
 // device and kept; it holds MPLB_NOALLOC_MAX_LATTICES items of any precision

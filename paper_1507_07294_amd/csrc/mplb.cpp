@@ -427,10 +427,11 @@ int mplb_time_stages(mplb_t* h, int nsteps, double ms[4]) {
 }
 
 // Instantiated graph of a chunk of batched steps, reused while the batch
-// keeps its shape (precision, walls, collision form, item count, block count,
-// steps, table).
+// keeps its shape (precision, kernel form, item count, block count, steps,
+// table).
 struct ChunkGraph {
-  int prec = -1, xywall = 0, nt = 0, unit = 0, count = 0, blocks = 0, nsteps = 0;
+  int prec = -1, count = 0, blocks = 0, nsteps = 0;
+  BatchForm form{};
   const void* table = nullptr;
   hipGraphExec_t exec = nullptr;
   unsigned long long used = 0;
@@ -465,13 +466,11 @@ int mplb_set_step_many_graphs(int enable) {
 
 // The cached graph for this chunk shape, built and instantiated on a miss
 // (replacing the least recently used entry).
-static int chunk_graph(mplb_t* h0, BatchTable& T, bool xywall, bool nt, bool unit, int count, int blocks,
-                       int nsteps, hipGraphExec_t* out) {
+static int chunk_graph(mplb_t* h0, BatchTable& T, const BatchForm& form, int count, int blocks, int nsteps,
+                       hipGraphExec_t* out) {
   ChunkGraph* slot = nullptr;
   for (auto& c : T.graphs)
-    if (c.exec && c.prec == h0->prec && c.xywall == (int)xywall && c.nt == (int)nt && c.unit == (int)unit &&
-        c.count == count &&
-        c.blocks == blocks &&
+    if (c.exec && c.prec == h0->prec && c.form == form && c.count == count && c.blocks == blocks &&
         c.nsteps == nsteps && c.table == T.dev)
       slot = &c;
   if (!slot) {
@@ -481,7 +480,7 @@ static int chunk_graph(mplb_t* h0, BatchTable& T, bool xywall, bool nt, bool uni
     if (slot->exec) HIPCHK(h0, hipGraphExecDestroy(slot->exec));
     slot->exec = nullptr;
     hipGraph_t g = nullptr;
-    HIPCHK(h0, build_fused_many_graph(h0->prec, xywall, nt, unit, T.dev, count, blocks, nsteps, &g));
+    HIPCHK(h0, build_fused_many_graph(h0->prec, form, T.dev, count, blocks, nsteps, &g));
     hipError_t e = hipGraphInstantiate(&slot->exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) {
@@ -489,9 +488,7 @@ static int chunk_graph(mplb_t* h0, BatchTable& T, bool xywall, bool nt, bool uni
       return fail(h0, MPLB_E_DEVICE, "graph instantiate: %s", hipGetErrorString(e));
     }
     slot->prec = h0->prec;
-    slot->xywall = xywall;
-    slot->nt = nt;
-    slot->unit = unit;
+    slot->form = form;
     slot->count = count;
     slot->blocks = blocks;
     slot->nsteps = nsteps;
@@ -522,7 +519,7 @@ static int check_after(mplb_t* const* hs, int count, int nsteps) {
 // Upload of a batch table without allocating: items are written into a stack
 // buffer and copied in pieces.  The copies are from pageable memory, so each
 // returns only once its bytes have left the buffer.
-static int upload_table_noalloc(mplb_t* const* hs, int count, void* dtab, hipStream_t s, int* blocks_out) {
+static int upload_table_noalloc(mplb_t* const* hs, int count, Bricks br, void* dtab, hipStream_t s, int* blocks_out) {
   mplb_t* h0 = hs[0];
   const size_t item = fused_batch_item_bytes(h0->prec);
   alignas(64) unsigned char stage[16384];
@@ -533,7 +530,7 @@ static int upload_table_noalloc(mplb_t* const* hs, int count, void* dtab, hipStr
     const int n = count - first < per ? count - first : per;
     for (int j = 0; j < n; ++j) {
       mplb_t* h = hs[first + j];
-      int nb = fused_batch_fill(h->prec, stage, j, h->G, h->C, h->B, h->cur, blocks);
+      int nb = fused_batch_fill(h->prec, stage, j, h->G, h->C, h->B, h->cur, blocks, br);
       if (nb <= 0) return fail(h0, MPLB_E_INVAL, "bad batch item");
       blocks += nb;
     }
@@ -584,21 +581,31 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   int dev = 0;
   HIPCHK(h0, hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(h0, MPLB_E_DEVICE, "device index out of range");
-  bool xywall = false;
+  bool xywall = false, zwall = false;
   size_t step_bytes = 0;
+  long long nodes = 0, padded[3] = {0, 0, 0};
   for (int i = 0; i < count; ++i) {
-    xywall = xywall || hs[i]->G.wall_x || hs[i]->G.wall_y;
-    step_bytes += fused_step_bytes(hs[i]->prec, hs[i]->mode, hs[i]->G.N);
+    const Geo& G = hs[i]->G;
+    xywall = xywall || G.wall_x || G.wall_y;
+    zwall = zwall || G.wall_z;
+    step_bytes += fused_step_bytes(hs[i]->prec, hs[i]->mode, G.N);
+    nodes += G.N;
+    padded[kBricksNarrow] += (long long)kBrickThreadsNarrow * brick_blocks(G, kBricksNarrow);
+    padded[kBricksWide] += (long long)kBrickThreadsWide * brick_blocks(G, kBricksWide);
   }
-  const bool nt = step_bytes > fused_stream_threshold();
+  BatchForm form{};
+  form.bricks = batch_bricks(h0->prec, step_bytes, nodes, padded);
+  form.wall = xywall || (form.bricks != kBricksNone && zwall);
+  form.nt = form.bricks == kBricksNone && step_bytes > fused_stream_threshold();
+  form.unit = unit;
   if (noalloc) {
     void* dtab = nullptr;
     HIPCHK(h0, noalloc_table(dev, &dtab));
     int blocks = 0;
-    int rc = upload_table_noalloc(hs, count, dtab, s, &blocks);
+    int rc = upload_table_noalloc(hs, count, form.bricks, dtab, s, &blocks);
     if (rc) return rc;
     for (int k = 0; k < nsteps; ++k)
-      HIPCHK(h0, launch_fused_many(h0->prec, xywall, nt, unit, dtab, count, blocks, k & 1, s));
+      HIPCHK(h0, launch_fused_many(h0->prec, form, dtab, count, blocks, k & 1, s));
   } else {
     BatchTable& T = g_tables[dev];
     size_t bytes = fused_batch_item_bytes(h0->prec) * (size_t)count;
@@ -625,7 +632,7 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
     int blocks = 0;
     for (int i = 0; i < count; ++i) {
       mplb_t* h = hs[i];
-      int nb = fused_batch_fill(h->prec, T.host, i, h->G, h->C, h->B, h->cur, blocks);
+      int nb = fused_batch_fill(h->prec, T.host, i, h->G, h->C, h->B, h->cur, blocks, form.bricks);
       if (nb <= 0) return fail(h0, MPLB_E_INVAL, "bad batch item");
       blocks += nb;
     }
@@ -635,12 +642,12 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
     HIPCHK(h0, hipEventRecord(T.uploaded, s));
     if (g_use_graphs && nsteps > 1) {
       hipGraphExec_t ex = nullptr;
-      int rc = chunk_graph(h0, T, xywall, nt, unit, count, blocks, nsteps, &ex);
+      int rc = chunk_graph(h0, T, form, count, blocks, nsteps, &ex);
       if (rc) return rc;
       HIPCHK(h0, hipGraphLaunch(ex, s));
     } else {
       for (int k = 0; k < nsteps; ++k)
-        HIPCHK(h0, launch_fused_many(h0->prec, xywall, nt, unit, T.dev, count, blocks, k & 1, s));
+        HIPCHK(h0, launch_fused_many(h0->prec, form, T.dev, count, blocks, k & 1, s));
     }
     HIPCHK(h0, hipEventRecord(T.done, s));
   }
