@@ -30,25 +30,27 @@ namespace {
 
 using namespace dev;
 
+// Buffer accesses at a byte offset per lane plus a scalar one (the start of an
+// array): array offsets cost no vector instruction.
 template <class S>
-__device__ inline S ld_off(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+__device__ inline S ld_off(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
   if constexpr (sizeof(S) == 2) {
-    return __builtin_bit_cast(S, (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0));
+    return __builtin_bit_cast(S, (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, off, soff, 0));
   } else if constexpr (sizeof(S) == 4) {
-    return __builtin_bit_cast(S, (unsigned int)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    return __builtin_bit_cast(S, (unsigned int)__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
   } else {
-    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
   }
 }
 template <class S>
-__device__ inline void st_off(__amdgpu_buffer_rsrc_t r, uint32_t off, S v) {
+__device__ inline void st_off(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff, S v) {
   if constexpr (sizeof(S) == 2) {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, off, soff, 0);
   } else if constexpr (sizeof(S) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, soff, 0);
   } else {
     using U2 = unsigned int __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, soff, 0);
   }
 }
 
@@ -65,64 +67,76 @@ __device__ inline int near_axis(int v, int n, int wall) {
   return v;
 }
 
-// A lattice node with the index steps to the sources of its pulls: s[a][0]
-// leads to the node a population with c_a = +1 comes from (x_a - 1, wrapped),
-// s[a][1] to that with c_a = -1; b likewise says that the population comes
-// through a wall of axis a.
-struct Node {
-  int n;
-  int s[3][2];
-  bool b[3][2];
+// A brick padded by H nodes on every side, and its halo positions.
+template <int BX, int BY, int BZ, int H>
+struct Pad {
+  static constexpr int PX = BX + 2 * H, PY = BY + 2 * H, PZ = BZ + 2 * H;
+  static constexpr int PXY = PX * PY, NPHI = PXY * PZ;
+  static constexpr int NT = BX * BY * BZ, NHALO = NPHI - NT;
+  static constexpr int HPT = (NHALO + NT - 1) / NT;
+
+  // Halo position h: first the whole rows above, below, before and behind the
+  // brick, then the 2 H columns at the sides of the brick's own rows (each of
+  // those a cache line of its own).
+  __device__ static void pos(int h, int& px, int& py, int& pz) {
+    constexpr int ZROWS = 2 * H * PY, ROWS = PY * PZ - BY * BZ;
+    if (h < ROWS * PX) {
+      const int r = h / PX;
+      px = h % PX;
+      if (r < ZROWS) {
+        pz = r / PY;
+        py = r % PY;
+        if (pz >= H) pz += BZ;
+      } else {
+        pz = H + (r - ZROWS) / (2 * H);
+        py = (r - ZROWS) % (2 * H);
+        if (py >= H) py += BY;
+      }
+    } else {
+      h -= ROWS * PX;
+      px = h % (2 * H);
+      if (px >= H) px += BX;
+      py = H + h / (2 * H) % BY;
+      pz = H + h / (2 * H) / BY;
+    }
+  }
 };
 
-// Node of lattice position (x, y, z), at most two nodes outside the lattice.
-template <bool WALL>
-__device__ inline Node make_node(const Geo& G, int x, int y, int z) {
-  Node d;
-  x = near_axis(x, G.nx, WALL && G.wall_x);
-  y = near_axis(y, G.ny, WALL && G.wall_y);
-  z = near_axis(z, G.nz, WALL && G.wall_z);
-  const int nxy = G.nx * G.ny;
-  d.n = x + G.nx * y + nxy * z;
-  d.s[0][0] = x == 0 ? G.nx - 1 : -1;
-  d.s[0][1] = x == G.nx - 1 ? 1 - G.nx : 1;
-  d.s[1][0] = y == 0 ? nxy - G.nx : -G.nx;
-  d.s[1][1] = y == G.ny - 1 ? G.nx - nxy : G.nx;
-  d.s[2][0] = z == 0 ? G.N - nxy : -nxy;
-  d.s[2][1] = z == G.nz - 1 ? nxy - G.N : nxy;
-  if constexpr (WALL) {
-    d.b[0][0] = G.wall_x && x == 0;
-    d.b[0][1] = G.wall_x && x == G.nx - 1;
-    d.b[1][0] = G.wall_y && y == 0;
-    d.b[1][1] = G.wall_y && y == G.ny - 1;
-    d.b[2][0] = G.wall_z && z == 0;
-    d.b[2][1] = G.wall_z && z == G.nz - 1;
+// Where the pulls of a coordinate along one axis come from, as byte offsets
+// into the arrays of f_1..f_6 (element type QS): the coordinate itself, the
+// source of a population with c_a = +1 (coordinate - 1, wrapped) and of one
+// with c_a = -1.  The last two count from the array of the +1 population (the
+// -1 one is the next array), so that a bounce at a wall, the node itself in
+// the other array, is an offset like any other.  bounce: bit 0 for c_a = +1,
+// bit 1 for c_a = -1.
+struct __align__(16) Axis {
+  uint32_t at, plus, minus, bounce;
+};
+
+// The block's table of Axis entries, for each coordinate of the padded brick
+// (x, then y, then z).  A position then costs three LDS reads and ten
+// additions; wrapping its own coordinates and testing them for walls took
+// about 90 vector instructions.
+template <class QS, class D, int H>
+__device__ inline void fill_axes(const Geo& G, int x0, int y0, int z0, Axis* tab) {
+  for (int t = threadIdx.x; t < D::PX + D::PY + D::PZ; t += D::NT) {
+    int v, n, stride, wall;
+    if (t < D::PX) v = x0 - H + t, n = G.nx, stride = 1, wall = G.wall_x;
+    else if (t < D::PX + D::PY) v = y0 - H + t - D::PX, n = G.ny, stride = G.nx, wall = G.wall_y;
+    else v = z0 - H + t - D::PX - D::PY, n = G.nz, stride = G.nx * G.ny, wall = G.wall_z;
+    const int m = near_axis(v, n, wall);
+    const bool first = m == 0, last = m == n - 1;
+    const bool bp = wall && first, bm = wall && last;
+    const uint32_t next = (uint32_t)G.pitch;
+    const uint32_t p = (uint32_t)((bp ? m : first ? n - 1 : m - 1) * stride) + (bp ? next : 0u);
+    const uint32_t q = (uint32_t)((bm ? m : last ? 0 : m + 1) * stride) + (bm ? 0u : next);
+    constexpr uint32_t sz = sizeof(QS);
+    tab[t] = Axis{(uint32_t)(m * stride) * sz, p * sz, q * sz, (bp ? 1u : 0u) | (bm ? 2u : 0u)};
   }
-  return d;
 }
 
-// Element index of the pull of population i (velocity c) into node d, in a
-// run of arrays `pitch` apart whose array `slot` holds population i and
-// `oslot` the opposite one.  32 bits hold it, in bytes too: the host takes
-// this kernel only for buffers below 4 GiB.
-template <bool WALL>
-__device__ inline uint32_t pull_at(const Node& d, uint32_t pitch, int cx, int cy, int cz, uint32_t slot,
-                                   uint32_t oslot) {
-  int idx = d.n;
-  if (cx != 0) idx += d.s[0][cx < 0];
-  if (cy != 0) idx += d.s[1][cy < 0];
-  if (cz != 0) idx += d.s[2][cz < 0];
-  const uint32_t at = slot * pitch + (uint32_t)idx;
-  if constexpr (WALL) {
-    bool b = false;
-    if (cx != 0) b = b || d.b[0][cx < 0];
-    if (cy != 0) b = b || d.b[1][cy < 0];
-    if (cz != 0) b = b || d.b[2][cz < 0];
-    return b ? oslot * pitch + (uint32_t)d.n : at;
-  }
-  return at;
-}
-
+// f of one position as stored: f_0 in r0, f_1..f_6 in r (PACK: words that
+// carry g_1..g_6 in their high halves).
 template <int P, bool PACK>
 struct Raw7 {
   using L = Lat<P, PACK>;
@@ -131,17 +145,29 @@ struct Raw7 {
   QS r[6];
 };
 
+// Offsets of the pulls along the axes: o[i - 1] for population i = 1..6.
+__device__ inline void face_offsets(const Axis& x, const Axis& y, const Axis& z, uint32_t o[6]) {
+  const uint32_t xy = x.at + y.at, yz = y.at + z.at, xz = x.at + z.at;
+  o[0] = yz + x.plus;
+  o[1] = yz + x.minus;
+  o[2] = xz + y.plus;
+  o[3] = xz + y.minus;
+  o[4] = xy + z.plus;
+  o[5] = xy + z.minus;
+}
+
 // rf: the f buffer from its start, ri: from the arrays of f_1..f_6
-template <int P, bool PACK, bool WALL>
-__device__ inline void pull7(__amdgpu_buffer_rsrc_t rf, __amdgpu_buffer_rsrc_t ri, uint32_t pitch, const Node& d,
-                             Raw7<P, PACK>& o) {
-  using L = Lat<P, PACK>;
+template <int P, bool PACK>
+__device__ inline void pull7(__amdgpu_buffer_rsrc_t rf, __amdgpu_buffer_rsrc_t ri, uint32_t pitch, const Axis& x,
+                             const Axis& y, const Axis& z, Raw7<P, PACK>& o) {
+  using S0 = typename Lat<P, PACK>::S0;
   using QS = typename Raw7<P, PACK>::QS;
-  o.r0 = ld_off<typename L::S0>(rf, (uint32_t)d.n * (uint32_t)sizeof(typename L::S0));
+  static_assert(sizeof(S0) % sizeof(QS) == 0, "f_0 at a multiple of the others' offset");
+  o.r0 = ld_off<S0>(rf, (x.at + y.at + z.at) * (uint32_t)(sizeof(S0) / sizeof(QS)), 0);
+  uint32_t off[6];
+  face_offsets(x, y, z, off);
 #pragma unroll
-  for (int i = 1; i < 7; ++i)
-    o.r[i - 1] = ld_off<QS>(ri, pull_at<WALL>(d, pitch, c7(i, 0), c7(i, 1), c7(i, 2), i - 1, opp(i) - 1) *
-                                    (uint32_t)sizeof(QS));
+  for (int i = 0; i < 6; ++i) o.r[i] = ld_off<QS>(ri, off[i], (uint32_t)(i / 2) * 2 * pitch * (uint32_t)sizeof(QS));
 }
 
 template <int P, bool PACK>
@@ -156,41 +182,45 @@ __device__ inline void cvt7(const Raw7<P, PACK>& o, typename Prec<P>::T f[7]) {
   }
 }
 
-// A brick padded by H nodes on every side, and its halo positions.
-template <int BX, int BY, int BZ, int H>
-struct Pad {
-  static constexpr int PX = BX + 2 * H, PY = BY + 2 * H, PZ = BZ + 2 * H;
-  static constexpr int PXY = PX * PY, NPHI = PXY * PZ;
-  static constexpr int NT = BX * BY * BZ, NHALO = NPHI - NT;
-  static constexpr int HPT = (NHALO + NT - 1) / NT;
-
-  // halo position h: H planes below and above the brick, then the frames of
-  // the planes between, H rows at each end and H columns at each side
-  __device__ static void pos(int h, int& px, int& py, int& pz) {
-    constexpr int CAP = H * PXY, FRAME = PXY - BX * BY;
-    if (h < 2 * CAP) {
-      pz = h / PXY;
-      const int r = h % PXY;
-      py = r / PX;
-      px = r % PX;
-      if (pz >= H) pz += BZ;
-      return;
-    }
-    h -= 2 * CAP;
-    pz = H + h / FRAME;
-    h %= FRAME;
-    if (h < 2 * H * PX) {
-      py = h / PX;
-      px = h % PX;
-      if (py >= H) py += BY;
-      return;
-    }
-    h -= 2 * H * PX;
-    py = H + h / (2 * H);
-    const int c = h % (2 * H);
-    px = c < H ? c : BX + c;
+// The g of the brick's own node (PACK: g_0 and g_7 on, at half the offsets of
+// the packed words).  The faces come from where f_1..f_6 do; the others, also
+// stored in antipodal pairs, bounce if any of their axes does.
+template <int P, bool PACK, bool WALL, int Q>
+__device__ inline void pull_own_g(__amdgpu_buffer_rsrc_t rg, uint32_t pitch, const Axis& x, const Axis& y,
+                                  const Axis& z, typename Lat<P, PACK>::S g[Q]) {
+  using L = Lat<P, PACK>;
+  using S = typename L::S;
+  using QS = typename Raw7<P, PACK>::QS;
+  constexpr uint32_t half = sizeof(QS) / sizeof(S);
+  const uint32_t arr = pitch * (uint32_t)sizeof(S), next = pitch * (uint32_t)sizeof(QS);
+  const uint32_t n = x.at + y.at + z.at;
+  g[0] = ld_off<S>(rg, n / half, 0);
+  if constexpr (!PACK) {
+    uint32_t off[6];
+    face_offsets(x, y, z, off);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) g[i + 1] = ld_off<S>(rg, off[i], (uint32_t)(1 + i / 2 * 2) * arr);
   }
-};
+  // sources of the diagonal velocities, without the step to the next array
+  const uint32_t sx[3] = {x.minus - next, x.at, x.plus}, sy[3] = {y.minus - next, y.at, y.plus},
+                 sz[3] = {z.minus - next, z.at, z.plus};
+#pragma unroll
+  for (int i = 7; i < Q; ++i) {
+    const int cx = cq<Q>(i, 0), cy = cq<Q>(i, 1), cz = cq<Q>(i, 2);
+    uint32_t at = sx[cx + 1] + sy[cy + 1] + sz[cz + 1];
+    const int first = i & 1 ? i : i - 1;  // of the antipodal pair
+    if constexpr (WALL) {
+      uint32_t b = 0;
+      if (cx != 0) b |= x.bounce & (cx > 0 ? 1u : 2u);
+      if (cy != 0) b |= y.bounce & (cy > 0 ? 1u : 2u);
+      if (cz != 0) b |= z.bounce & (cz > 0 ? 1u : 2u);
+      at = i == first ? (b ? n + next : at) : (b ? n : at + next);
+      g[i] = ld_off<S>(rg, at / half, (uint32_t)L::gslot(first) * arr);
+    } else {
+      g[i] = ld_off<S>(rg, at / half, (uint32_t)L::gslot(i) * arr);
+    }
+  }
+}
 
 // Brick lb of the lattice: its first node, bricks ordered x, y, z.
 template <int BX, int BY, int BZ>
@@ -211,28 +241,33 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   using L = Lat<P, PACK>;
   using S = typename L::S;
   using S0 = typename L::S0;
+  using QS = typename Raw7<P, PACK>::QS;
   using D = Pad<BX, BY, BZ, 2>;
   using M1 = Pad<BX, BY, BZ, 1>;
   constexpr int NT = D::NT;
+  static_assert(sizeof(T) == sizeof(QS) && sizeof(S0) == sizeof(QS), "one offset for f, f_0 and the history");
   __shared__ T sphi[D::NPHI];
   __shared__ T smu[M1::NPHI];
+  __shared__ Axis tab[D::PX + D::PY + D::PZ];
   if (C.poison) {
     poison_shared(sphi, sizeof sphi);
     poison_shared(smu, sizeof smu);
+    poison_shared(tab, sizeof tab);
     __syncthreads();
   }
   int x0, y0, z0;
   brick_origin<BX, BY, BZ>(G, lb, x0, y0, z0);
+  fill_axes<QS, D, 2>(G, x0, y0, z0, tab);
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX % BY, tz = tid / (BX * BY);
-  const int gx = x0 + tx, gy = y0 + ty, gz = z0 + tz;
-  const bool own = gx < G.nx && gy < G.ny && gz < G.nz;
-  const uint32_t pitch = (uint32_t)G.pitch;
+  const bool own = x0 + tx < G.nx && y0 + ty < G.ny && z0 + tz < G.nz;
+  const uint32_t pitch = (uint32_t)G.pitch, arr = pitch * (uint32_t)sizeof(T);
   const void* fin = cur ? B.f[1] : B.f[0];
   const void* gin = cur ? B.g[1] : B.g[0];
   void* fo = cur ? B.f[0] : B.f[1];
   void* go = cur ? B.g[0] : B.g[1];
   const auto rf = rsrc_at(fin), ri = rsrc_at(L::fi(fin, G.pitch)), rg = rsrc_at(gin), rh = rsrc_at(B.phiu);
+  __syncthreads();
 
   // every load of the step: the node's own f, the f of its halo positions, g
   // and the history.  Every lane loads (a lane without a node or a position
@@ -240,9 +275,10 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   // of loads in flight unknown, and phi would wait for the g as well (32^3
   // FP32 6.6 -> 6.1 us per step, W = 48 box with 16-bit populations 19.2 ->
   // 16.8 us).
-  const Node me = make_node<WALL>(G, gx, gy, gz);
+  const Axis ax = tab[tx + 2], ay = tab[D::PX + ty + 2], az = tab[D::PX + D::PY + tz + 2];
+  const uint32_t n = ax.at + ay.at + az.at;
   Raw7<P, PACK> fr;
-  pull7<P, PACK, WALL>(rf, ri, pitch, me, fr);
+  pull7<P, PACK>(rf, ri, pitch, ax, ay, az, fr);
   Raw7<P, PACK> hr[D::HPT];
   int hat[D::HPT];
 #pragma unroll
@@ -250,53 +286,49 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
     const int h = tid + k * NT;
     int px, py, pz;
     D::pos(h < D::NHALO ? h : D::NHALO - 1, px, py, pz);
-    const int hx = x0 - 2 + px, hy = y0 - 2 + py, hz = z0 - 2 + pz;
-    hat[k] = h < D::NHALO ? px + D::PX * py + D::PXY * pz : -1;
-    const Node hn = make_node<WALL>(G, hx, hy, hz);
-    pull7<P, PACK, WALL>(rf, ri, pitch, hn, hr[k]);
+    hat[k] = px + D::PX * py + D::PXY * pz;
+    pull7<P, PACK>(rf, ri, pitch, tab[px], tab[D::PX + py], tab[D::PX + D::PY + pz], hr[k]);
   }
   S gr[Q];
   T hp[3];
-  gr[0] = ld_off<S>(rg, (uint32_t)me.n * (uint32_t)sizeof(S));
+  pull_own_g<P, PACK, WALL, Q>(rg, pitch, ax, ay, az, gr);
 #pragma unroll
-  for (int i = PACK ? 7 : 1; i < Q; ++i)
-    gr[i] = ld_off<S>(rg, pull_at<WALL>(me, pitch, cq<Q>(i, 0), cq<Q>(i, 1), cq<Q>(i, 2), (uint32_t)L::gslot(i),
-                                        (uint32_t)L::gslot(opp(i))) * (uint32_t)sizeof(S));
-#pragma unroll
-  for (int a = 0; a < 3; ++a) hp[a] = ld_off<T>(rh, (a * pitch + (uint32_t)me.n) * (uint32_t)sizeof(T));
+  for (int a = 0; a < 3; ++a) hp[a] = ld_off<T>(rh, n, (uint32_t)a * arr);
   __builtin_amdgcn_sched_barrier(0);
 
   // phi of the padded brick
   T f[7];
   cvt7<P, PACK>(fr, f);
   const T phi = phi_of(f);
-  sphi[(tx + 2) + D::PX * (ty + 2) + D::PXY * (tz + 2)] = phi;
+  const int pat = (tx + 2) + D::PX * (ty + 2) + D::PXY * (tz + 2);
+  sphi[pat] = phi;
 #pragma unroll
   for (int k = 0; k < D::HPT; ++k) {
-    if (hat[k] >= 0) {
+    if (tid + k * NT < D::NHALO) {
       T fh[7];
       cvt7<P, PACK>(hr[k], fh);
       sphi[hat[k]] = phi_of(fh);
     }
   }
   __syncthreads();
-  // mu of the brick and a halo of one; a ghost position of a wall takes its
-  // mirror image
-  constexpr int MPT = (M1::NPHI + NT - 1) / NT;
+  // mu of the brick (k = 0) and of a halo of one; a ghost position of a wall
+  // takes its mirror image
 #pragma unroll
-  for (int k = 0; k < MPT; ++k) {
-    const int q = tid + k * NT;
-    const int qz = q / M1::PXY, r = q % M1::PXY, qy = r / M1::PX, qx = r % M1::PX;
-    int mx = x0 - 1 + qx, my = y0 - 1 + qy, mz = z0 - 1 + qz;
-    if (q < M1::NPHI && mx <= G.nx && my <= G.ny && mz <= G.nz) {
-      if (WALL && G.wall_x) mx = clamp_axis(mx, G.nx);
-      if (WALL && G.wall_y) my = clamp_axis(my, G.ny);
-      if (WALL && G.wall_z) mz = clamp_axis(mz, G.nz);
-      const int at = (mx - (x0 - 2)) + D::PX * (my - (y0 - 2));
-      const T* pc = sphi + D::PXY * (mz - (z0 - 2));
-      const T c0 = pc[at];
-      const T lap = lap_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, at);
-      smu[q] = 4 * C.beta * c0 * (c0 - 1) * (c0 + 1) - C.kappa * lap;
+  for (int k = 0; k <= M1::HPT; ++k) {
+    const int h = tid + (k - 1) * NT;
+    if (k == 0 || h < M1::NHALO) {
+      int qx = tx + 1, qy = ty + 1, qz = tz + 1;
+      if (k > 0) M1::pos(h, qx, qy, qz);
+      int sx = qx + 1, sy = qy + 1, sz = qz + 1;
+      if constexpr (WALL) {
+        if (G.wall_x) sx = clamp_axis(x0 - 1 + qx, G.nx) - (x0 - 2);
+        if (G.wall_y) sy = clamp_axis(y0 - 1 + qy, G.ny) - (y0 - 2);
+        if (G.wall_z) sz = clamp_axis(z0 - 1 + qz, G.nz) - (z0 - 2);
+      }
+      const T* pc = sphi + (sx + D::PX * sy + D::PXY * sz);
+      const T c0 = pc[0];
+      const T lap = lap_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, 0);
+      smu[qx + M1::PX * qy + M1::PXY * qz] = 4 * C.beta * c0 * (c0 - 1) * (c0 + 1) - C.kappa * lap;
     }
   }
   __syncthreads();
@@ -310,13 +342,12 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   g[0] = (T)gr[0];
 #pragma unroll
   for (int i = PACK ? 7 : 1; i < Q; ++i) g[i] = (T)gr[i];
-  const int pat = (tx + 2) + D::PX * (ty + 2), mat = (tx + 1) + M1::PX * (ty + 1);
-  const T* pc = sphi + D::PXY * (tz + 2);
-  const T* mc = smu + M1::PXY * (tz + 1);
+  const T* pc = sphi + pat;
+  const T* mc = smu + ((tx + 1) + M1::PX * (ty + 1) + M1::PXY * (tz + 1));
   T gphi[3];
-  grad_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, pat, gphi);
-  const T mu = mc[mat];
-  const T lapmu = lap_lds<T, M1::PX>(mc - M1::PXY, mc, mc + M1::PXY, mat);
+  grad_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, 0, gphi);
+  const T mu = mc[0];
+  const T lapmu = lap_lds<T, M1::PX>(mc - M1::PXY, mc, mc + M1::PXY, 0);
   Macro<T> M;
   if constexpr (Q == 19) flow_macro19(C, g, phi, mu, gphi, lapmu, M);
   else flow_macro(C, g, phi, mu, gphi, lapmu, M);
@@ -325,25 +356,23 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   for (int a = 0; a < 3; ++a) {
     const T pu = phi * M.u[a];
     dphiu[a] = pu - hp[a];
-    st_off<T>(rh, (a * pitch + (uint32_t)me.n) * (uint32_t)sizeof(T), pu);
+    st_off<T>(rh, n, (uint32_t)a * arr, pu);
   }
   collide_che(C, f, phi, mu, M.u, dphiu);
   if constexpr (Q == 19) collide_ns19(C, g, M);
   else collide_ns<false, (V & kVarUnit) != 0>(C, g, M);
   const auto wf = rsrc_at(fo), wi = rsrc_at(L::fi(fo, G.pitch)), wg = rsrc_at(go);
-  const uint32_t n = (uint32_t)me.n;
-  st_off<S0>(wf, n * (uint32_t)sizeof(S0), (S0)f[0]);
-  st_off<S>(wg, n * (uint32_t)sizeof(S), (S)g[0]);
-  if constexpr (PACK) {
+  constexpr uint32_t half = sizeof(QS) / sizeof(S);
+  const uint32_t ng = n / half, garr = pitch * (uint32_t)sizeof(S);
+  st_off<S0>(wf, n, 0, (S0)f[0]);
+  st_off<S>(wg, ng, 0, (S)g[0]);
 #pragma unroll
-    for (int i = 1; i < 7; ++i) st_off<uint32_t>(wi, ((i - 1) * pitch + n) * 4u, L::pack(f[i], g[i]));
-  } else {
-#pragma unroll
-    for (int i = 1; i < 7; ++i) st_off<S>(wi, ((i - 1) * pitch + n) * (uint32_t)sizeof(S), (S)f[i]);
+  for (int i = 1; i < 7; ++i) {
+    if constexpr (PACK) st_off<uint32_t>(wi, n, (uint32_t)(i - 1) * arr, L::pack(f[i], g[i]));
+    else st_off<S>(wi, n, (uint32_t)(i - 1) * arr, (S)f[i]);
   }
 #pragma unroll
-  for (int i = PACK ? 7 : 1; i < Q; ++i)
-    st_off<S>(wg, ((uint32_t)L::gslot(i) * pitch + n) * (uint32_t)sizeof(S), (S)g[i]);
+  for (int i = PACK ? 7 : 1; i < Q; ++i) st_off<S>(wg, ng, (uint32_t)L::gslot(i) * garr, (S)g[i]);
   if (!(all_finite(f, 7) && all_finite(g, Q))) *B.flag = 1;
 }
 
@@ -355,7 +384,7 @@ k_brick(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
 
 // The CHE-only step of a brick: mu at the node only, so phi needs a halo of
 // one, and the history is phi alone.
-template <int P, bool WALL, int BX, int BY, int BZ>
+template <int P, int BX, int BY, int BZ>
 __global__ void __launch_bounds__(BX* BY* BZ) __attribute__((amdgpu_waves_per_eu(waves_per_eu<P>())))
 k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   using T = typename Prec<P>::T;
@@ -369,13 +398,16 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   // sin(pi t / n) and sin(2 pi t / n) of the deformation flow at the brick's
   // coordinates, x then y then z
   __shared__ T sn[2][BX + BY + BZ];
+  __shared__ Axis tab[D::PX + D::PY + D::PZ];
   if (C.poison) {
     poison_shared(sphi, sizeof sphi);
     poison_shared(sn, sizeof sn);
+    poison_shared(tab, sizeof tab);
     __syncthreads();
   }
   int x0, y0, z0;
   brick_origin<BX, BY, BZ>(G, logical_block(blockIdx.x, gridDim.x), x0, y0, z0);
+  fill_axes<S, D, 1>(G, x0, y0, z0, tab);
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX % BY, tz = tid / (BX * BY);
   const int gx = x0 + tx, gy = y0 + ty, gz = z0 + tz;
@@ -384,10 +416,12 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   const void* fin = cur ? B.f[1] : B.f[0];
   void* fo = cur ? B.f[0] : B.f[1];
   const auto rf = rsrc_at(fin), ri = rsrc_at(L::fi(fin, G.pitch)), rh = rsrc_at(B.phiu);
-  const Node me = make_node<WALL>(G, gx, gy, gz);
-  const uint32_t n = (uint32_t)me.n;
+  __syncthreads();
+  const Axis ax = tab[tx + 1], ay = tab[D::PX + ty + 1], az = tab[D::PX + D::PY + tz + 1];
+  const uint32_t n = ax.at + ay.at + az.at;                       // f_1..f_6
+  const uint32_t n0 = n * (uint32_t)(sizeof(T) / sizeof(S));      // f_0 and the history
   Raw7<P, false> fr;
-  pull7<P, false, WALL>(rf, ri, pitch, me, fr);
+  pull7<P, false>(rf, ri, pitch, ax, ay, az, fr);
   Raw7<P, false> hr[D::HPT];
   int hat[D::HPT];
 #pragma unroll
@@ -397,18 +431,15 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
     if (h < D::NHALO) {
       int px, py, pz;
       D::pos(h, px, py, pz);
-      const int hx = x0 - 1 + px, hy = y0 - 1 + py, hz = z0 - 1 + pz;
-      if (hx <= G.nx && hy <= G.ny && hz <= G.nz) {
-        hat[k] = px + D::PX * py + D::PXY * pz;
-        const Node hn = make_node<WALL>(G, hx, hy, hz);
-        pull7<P, false, WALL>(rf, ri, pitch, hn, hr[k]);
-      }
+      hat[k] = px + D::PX * py + D::PXY * pz;
+      pull7<P, false>(rf, ri, pitch, tab[px], tab[D::PX + py], tab[D::PX + D::PY + pz], hr[k]);
     }
   }
   T phip = 0, u[3] = {0, 0, 0}, up[3] = {0, 0, 0};
   if (own) {
-    phip = ld_off<T>(rh, n * (uint32_t)sizeof(T));
-    if (C.vel_kind != MPLB_VEL_DEFORM) presc_u(G, C, (const T*)B.ufield, gx, gy, gz, me.n, u, up);
+    phip = ld_off<T>(rh, n0, 0);
+    if (C.vel_kind != MPLB_VEL_DEFORM)
+      presc_u(G, C, (const T*)B.ufield, gx, gy, gz, (int)(n / (uint32_t)sizeof(S)), u, up);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (C.vel_kind == MPLB_VEL_DEFORM && tid < 2 * (BX + BY + BZ)) {
@@ -422,7 +453,8 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   T f[7];
   cvt7<P, false>(fr, f);
   const T phi = phi_of(f);
-  sphi[(tx + 1) + D::PX * (ty + 1) + D::PXY * (tz + 1)] = phi;
+  const int pat = (tx + 1) + D::PX * (ty + 1) + D::PXY * (tz + 1);
+  sphi[pat] = phi;
 #pragma unroll
   for (int k = 0; k < D::HPT; ++k) {
     if (hat[k] >= 0) {
@@ -433,9 +465,8 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   }
   __syncthreads();
   if (!own) return;
-  const int at = (tx + 1) + D::PX * (ty + 1);
-  const T* pc = sphi + D::PXY * (tz + 1);
-  const T lap = lap_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, at);
+  const T* pc = sphi + pat;
+  const T lap = lap_lds<T, D::PX>(pc - D::PXY, pc, pc + D::PXY, 0);
   const T mu = 4 * C.beta * phi * (phi - 1) * (phi + 1) - C.kappa * lap;
   if (C.vel_kind == MPLB_VEL_DEFORM) {
     // the products in the order of PrescColumn
@@ -450,15 +481,15 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
       up[k] = b[k] * C.vel_ct_prev;
     }
   }
-  st_off<T>(rh, n * (uint32_t)sizeof(T), phi);
+  st_off<T>(rh, n0, 0, phi);
   T dphiu[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) dphiu[a] = phi * u[a] - phip * up[a];
   collide_che(C, f, phi, mu, u, dphiu);
   const auto wf = rsrc_at(fo), wi = rsrc_at(L::fi(fo, G.pitch));
-  st_off<S0>(wf, n * (uint32_t)sizeof(S0), (S0)f[0]);
+  st_off<S0>(wf, n0, 0, (S0)f[0]);
 #pragma unroll
-  for (int i = 1; i < 7; ++i) st_off<S>(wi, ((i - 1) * pitch + n) * (uint32_t)sizeof(S), (S)f[i]);
+  for (int i = 1; i < 7; ++i) st_off<S>(wi, n, (uint32_t)(i - 1) * pitch * (uint32_t)sizeof(S), (S)f[i]);
   if (!all_finite(f, 7)) *B.flag = 1;
 }
 
@@ -478,12 +509,21 @@ k_brick_many(const BatchItem<typename Prec<P>::T>* __restrict__ tab, int count, 
   brick_body<P, 15, WALL, V, BX, BY, BZ>(it.G, it.C, it.B, it.cur0 ^ flip, b - it.block0);
 }
 
-template <int P, bool WALL, int BX, int BY, int BZ>
-hipError_t brick_impl3(int mode, const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur, int blocks,
+// The brick sizes: 16 x 4 x 4, 16 x 8 x 4 and 32 x 4 x 4.
+constexpr int brick_x(Bricks br) { return br == kBricksWide ? 32 : 16; }
+constexpr int brick_y(Bricks br) { return br == kBricksMid ? 8 : 4; }
+static_assert(brick_x(kBricksNarrow) * brick_y(kBricksNarrow) * 4 == brick_threads(kBricksNarrow) &&
+                  brick_x(kBricksMid) * brick_y(kBricksMid) * 4 == brick_threads(kBricksMid) &&
+                  brick_x(kBricksWide) * brick_y(kBricksWide) * 4 == brick_threads(kBricksWide),
+              "one thread per node");
+
+template <int P, bool WALL, Bricks BR>
+hipError_t brick_impl3(int mode, const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur,
                        hipStream_t s) {
-  const dim3 grid((unsigned)blocks), block(BX * BY * BZ);
+  constexpr int BX = brick_x(BR), BY = brick_y(BR), BZ = 4;
+  const dim3 grid((unsigned)brick_blocks(G, BR)), block(brick_threads(BR));
   if (mode == MPLB_CHE_ONLY)
-    hipLaunchKernelGGL((k_brick_che<P, WALL, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
+    hipLaunchKernelGGL((k_brick_che<P, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
   else if (mode == MPLB_COUPLED_Q19)
     hipLaunchKernelGGL((k_brick<P, 19, WALL, 0, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
   else if (C.unit_rates)
@@ -493,17 +533,14 @@ hipError_t brick_impl3(int mode, const Geo& G, const Coef<typename Prec<P>::T>& 
   return hipGetLastError();
 }
 
-// Bricks are 4 nodes high and deep: 16 x 4 x 4 (256 threads) or 32 x 4 x 4.
-constexpr int brick_width(Bricks br) { return br == kBricksWide ? 32 : 16; }
-static_assert(brick_width(kBricksNarrow) * 16 == kBrickThreadsNarrow && brick_width(kBricksWide) * 16 == kBrickThreadsWide,
-              "one thread per node");
-
 template <int P, bool WALL>
 hipError_t brick_impl2(int mode, const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur, Bricks br,
                        hipStream_t s) {
-  const int blocks = brick_blocks(G, br);
-  if (br == kBricksWide) return brick_impl3<P, WALL, brick_width(kBricksWide), 4, 4>(mode, G, C, B, cur, blocks, s);
-  return brick_impl3<P, WALL, brick_width(kBricksNarrow), 4, 4>(mode, G, C, B, cur, blocks, s);
+  switch (br) {
+    case kBricksWide: return brick_impl3<P, WALL, kBricksWide>(mode, G, C, B, cur, s);
+    case kBricksMid: return brick_impl3<P, WALL, kBricksMid>(mode, G, C, B, cur, s);
+    default: return brick_impl3<P, WALL, kBricksNarrow>(mode, G, C, B, cur, s);
+  }
 }
 
 template <int P>
@@ -516,8 +553,11 @@ hipError_t brick_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs
 
 template <int P, bool WALL, int V>
 const void* brick_many3(Bricks br) {
-  return br == kBricksWide ? (const void*)k_brick_many<P, WALL, V, brick_width(kBricksWide), 4, 4>
-                           : (const void*)k_brick_many<P, WALL, V, brick_width(kBricksNarrow), 4, 4>;
+  switch (br) {
+    case kBricksWide: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksWide), brick_y(kBricksWide), 4>;
+    case kBricksMid: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksMid), brick_y(kBricksMid), 4>;
+    default: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksNarrow), brick_y(kBricksNarrow), 4>;
+  }
 }
 template <int P>
 const void* brick_many2(bool wall, bool unit, Bricks br) {
@@ -542,23 +582,26 @@ constexpr size_t kBrickBytes = (size_t)285000000, kBrickBytesCheF64 = (size_t)24
 // not so with partly empty tiles: 120^3 62.5 / 58.4, 112^3 52.4 / 49.9.
 constexpr long long kBrickNodes16 = 1200000;
 
-// Wide bricks where they cover at most 1.2 times the nodes that narrow ones
-// do: their rows are twice as long for the same halo.  FP32, narrow against
-// wide: 64^3 13.5 / 12.1, 72^3 (the 1.2) 20.1 / 19.2, 100^3 48.0 / 45.9; 48^3
-// (1.33) 8.6 / 10.2; CHE-only 128^3 34.0 / 29.1.  Below 100 k nodes narrow
-// bricks put twice as many CUs to work (32^3 6.1 / 7.0).  The coupled step in
-// FP64 keeps narrow ones, whose blocks of four waves fit a CU twice (72^3
-// 32.5 / 39.0).
-Bricks brick_kind(int P, int mode, long long nodes, long long narrow, long long wide) {
-  if (mode != MPLB_CHE_ONLY && P == MPLB_F64) return kBricksNarrow;
-  return nodes >= 100000 && 10 * wide <= 12 * narrow ? kBricksWide : kBricksNarrow;
+// Narrow bricks below 100 k nodes, where they put twice as many CUs to work
+// (32^3 FP32 6.3 us per step against 7.2 and 7.3 with the larger ones), and for
+// the coupled step in FP64, whose blocks of four waves fit a CU twice (72^3
+// 32.2 / 35.0 mid / 39.4 wide).  Otherwise wide ones, whose rows are a whole
+// cache line, where they cover at most 1.2 times the nodes that mid ones do
+// (1.1 with 16-bit populations), else mid ones.  Mid against wide: FP32
+// 64 x 64 x 256 40.1 / 36.2, 72^3 (1.2) 21.5 / 19.3, 48 x 48 x 192 (1.33)
+// 20.7 / 21.4; FP16 70 x 77 x 69 (1.2) 16.9 / 18.7, 100^3 (1.14) 34.9 / 35.3;
+// CHE-only FP32 128^3 29.3 / 27.1, FP64 64^3 9.5 / 9.0.
+Bricks brick_kind(int P, int mode, long long nodes, long long mid, long long wide) {
+  if (nodes < 100000 || (mode != MPLB_CHE_ONLY && P == MPLB_F64)) return kBricksNarrow;
+  const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
+  return 10 * wide <= (mode != MPLB_CHE_ONLY && bits16 ? 11 : 12) * mid ? kBricksWide : kBricksMid;
 }
 
 }  // namespace
 
 int brick_blocks(const Geo& G, Bricks br) {
-  const int bx = brick_width(br);
-  return ((G.nx + bx - 1) / bx) * ((G.ny + 3) / 4) * ((G.nz + 3) / 4);
+  const int bx = brick_x(br), by = brick_y(br);
+  return ((G.nx + bx - 1) / bx) * ((G.ny + by - 1) / by) * ((G.nz + 3) / 4);
 }
 
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
@@ -570,13 +613,13 @@ Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
     const long long tiles = (long long)((G.nx + 63) / 64 * 64) * ((G.ny + 7) / 8 * 8) * G.nz;
     if (10 * tiles < 11 * n) return kBricksNone;
   }
-  return brick_kind(P, mode, n, 256LL * brick_blocks(G, kBricksNarrow), 512LL * brick_blocks(G, kBricksWide));
+  return brick_kind(P, mode, n, 512LL * brick_blocks(G, kBricksMid), 512LL * brick_blocks(G, kBricksWide));
 }
 
-Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[3]) {
+Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[kBrickKinds]) {
   if (bytes > kBrickBytes) return kBricksNone;
   if ((P == MPLB_F32_F16 || P == MPLB_F32_BF16) && nodes > kBrickNodes16) return kBricksNone;
-  return brick_kind(P, MPLB_COUPLED, nodes, padded[kBricksNarrow], padded[kBricksWide]);
+  return brick_kind(P, MPLB_COUPLED, nodes, padded[kBricksMid], padded[kBricksWide]);
 }
 
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br) {

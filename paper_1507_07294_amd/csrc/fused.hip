@@ -1116,7 +1116,7 @@ const void* many_kernel(int P, const BatchForm& f) {
   }
 }
 unsigned many_threads(Bricks br) {
-  return br == kBricksNone ? kTX * kTY : (br == kBricksWide ? kBrickThreadsWide : kBrickThreadsNarrow);
+  return br == kBricksNone ? kTX * kTY : brick_threads(br);
 }
 
 template <int P>

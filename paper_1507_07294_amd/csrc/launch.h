@@ -19,16 +19,16 @@ hipError_t launch_fused_step(int P, int mode, const Geo& G, const Coef<double>& 
                              hipStream_t s, int rows = 0);
 // The same step in three-dimensional bricks, one thread per node (brick.hip),
 // for the lattices that step_bricks picks.
-enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksWide = 2 };
+enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksMid = 2, kBricksWide = 3, kBrickKinds = 4 };
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C);
 hipError_t launch_brick_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, Bricks br,
                              hipStream_t s);
 int brick_blocks(const Geo& G, Bricks br);
 // the same for a batch of D3Q15 lattices: `bytes` and `nodes` over the batch,
-// `padded` the nodes that bricks of either width cover (index Bricks)
-Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[3]);
+// `padded` the nodes that bricks of each kind cover
+Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[kBrickKinds]);
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br);
-constexpr int kBrickThreadsNarrow = 256, kBrickThreadsWide = 512;
+constexpr int brick_threads(Bricks br) { return br == kBricksNarrow ? 256 : 512; }
 // the kernel and work split of a marching step (host computation only; rows as
 // for launch_fused_step, assumed valid for P and mode)
 Shape launch_shape(int P, int mode, const Geo& G, int rows);

@@ -583,15 +583,15 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   if (dev < 0 || dev >= 64) return fail(h0, MPLB_E_DEVICE, "device index out of range");
   bool xywall = false, zwall = false;
   size_t step_bytes = 0;
-  long long nodes = 0, padded[3] = {0, 0, 0};
+  long long nodes = 0, padded[kBrickKinds] = {};
   for (int i = 0; i < count; ++i) {
     const Geo& G = hs[i]->G;
     xywall = xywall || G.wall_x || G.wall_y;
     zwall = zwall || G.wall_z;
     step_bytes += fused_step_bytes(hs[i]->prec, hs[i]->mode, G.N);
     nodes += G.N;
-    padded[kBricksNarrow] += (long long)kBrickThreadsNarrow * brick_blocks(G, kBricksNarrow);
-    padded[kBricksWide] += (long long)kBrickThreadsWide * brick_blocks(G, kBricksWide);
+    for (Bricks br : {kBricksNarrow, kBricksMid, kBricksWide})
+      padded[br] += (long long)brick_threads(br) * brick_blocks(G, br);
   }
   BatchForm form{};
   form.bricks = batch_bricks(h0->prec, step_bytes, nodes, padded);

@@ -1,7 +1,8 @@
 """The brick kernels (small lattices) against the marching ones, bit for bit: a
 node's arithmetic does not depend on the kernel that does it, and the marches
-are compared with the oracle elsewhere.  Boxes at the edges of the 16 x 4 x 4
-and 32 x 4 x 4 bricks, axes of one to three nodes, walls on every axis."""
+are compared with the oracle elsewhere.  Boxes at the edges of the 16 x 4 x 4,
+16 x 8 x 4 and 32 x 4 x 4 bricks, axes of one to three nodes, walls on every
+axis."""
 import numpy as np
 import pytest
 
@@ -10,11 +11,12 @@ from paper_1507_07294_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-# nx at the brick widths and their remainders, ny and nz at 4 and theirs; the
-# last three take the wide bricks (100 k nodes and a fitting width)
+# nx at the brick widths and their remainders, ny and nz at 4 and 8 and theirs;
+# the last four have 100 k nodes and more: 32 x 4 x 4 bricks, the 48-wide box
+# 16 x 8 x 4
 BOXES = [((1, 1, 1), (0, 0, 0)), ((1, 5, 2), (1, 0, 0)), ((2, 3, 9), (0, 1, 1)), ((15, 4, 4), (0, 0, 0)),
          ((16, 8, 5), (0, 0, 1)), ((17, 3, 13), (1, 1, 1)), ((33, 9, 6), (0, 1, 0)), ((31, 61, 62), (0, 0, 1)),
-         ((64, 41, 43), (1, 1, 1)), ((96, 35, 34), (0, 0, 0))]
+         ((64, 41, 43), (1, 1, 1)), ((96, 35, 34), (0, 0, 0)), ((48, 46, 49), (0, 1, 1))]
 
 
 def _fields(w, precision, steps, rows, one_by_one):
@@ -46,10 +48,10 @@ def test_bricks_equal_the_march(kind, precision):
 
 @pytest.mark.parametrize("precision", ["f64", "f32", "f16"])
 def test_small_batches_equal_their_lattices_alone(precision):
-    """A batch that steps in bricks (narrow, and wide from 100 k nodes), with
+    """A batch that steps in bricks (narrow, and larger from 100 k nodes), with
     and without walls, both collision forms, odd and even step counts."""
     for unit in (False, True):
-        for boxes in (BOXES[:7], BOXES[7:], [b for b in BOXES if b[1] == (0, 0, 0)]):
+        for boxes in (BOXES[:7], BOXES[7:], BOXES[10:], [b for b in BOXES if b[1] == (0, 0, 0)]):
             ws = [wl.perturbed_case(s, bc, 70 + i, sigma=1e-3) for i, (s, bc) in enumerate(boxes)]
             if unit:
                 for w in ws:
