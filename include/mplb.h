@@ -201,10 +201,14 @@ int mplb_totals(mplb_t* h, double out[7]);
  * state. */
 int mplb_front(mplb_t* h, double out[2]);
 
-/* Advance `count` lattices by nsteps each with batched launches: one kernel
- * per step covers every coupled lattice (continuous-batching serving); the
- * nsteps launches are replayed as one HIP graph, cached while the batch keeps
- * its shape.  Each lattice computes exactly what mplb_step computes for it.
+/* Advance `count` lattices by nsteps each with batched launches
+ * (continuous-batching serving): one kernel per step covers every coupled
+ * lattice of a group.  A call of few steps has one group; a longer one gathers
+ * small lattices into groups whose state stays in the last-level cache, each
+ * group doing its nsteps before the next, and larger ones into a group of
+ * their own.  The launches of a batch of one group are replayed as one HIP
+ * graph, cached while the batch keeps its shape.  Each lattice computes
+ * exactly what mplb_step computes for it.
  * All handles must be initialised, share one precision and mode, and use the
  * first handle's stream (MPLB_E_INVAL otherwise, before anything is
  * enqueued).  Not thread-safe across calls on one device.

@@ -597,6 +597,11 @@ Bricks brick_kind(int P, int mode, long long nodes, long long mid, long long wid
   return 10 * wide <= (mode != MPLB_CHE_ONLY && bits16 ? 11 : 12) * mid ? kBricksWide : kBricksMid;
 }
 
+// nodes that 64 x 8 marching tiles cover
+long long march_nodes(const Geo& G) {
+  return (long long)((G.nx + 63) / 64 * 64) * ((G.ny + 7) / 8 * 8) * G.nz;
+}
+
 }  // namespace
 
 int brick_blocks(const Geo& G, Bricks br) {
@@ -604,22 +609,33 @@ int brick_blocks(const Geo& G, Bricks br) {
   return ((G.nx + bx - 1) / bx) * ((G.ny + by - 1) / by) * ((G.nz + 3) / 4);
 }
 
+size_t brick_bytes_limit(int P, int mode) {
+  return mode == MPLB_CHE_ONLY && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes;
+}
+
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
   if (C.stencil7 || C.forcing28) return kBricksNone;  // the study variants are marching kernels
   const long long n = (long long)G.nx * G.ny * G.nz;
-  const bool che = mode == MPLB_CHE_ONLY;
-  if (fused_step_bytes(P, mode, n) > (che && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes)) return kBricksNone;
-  if (!che && (P == MPLB_F32_F16 || P == MPLB_F32_BF16) && n > kBrickNodes16) {
-    const long long tiles = (long long)((G.nx + 63) / 64 * 64) * ((G.ny + 7) / 8 * 8) * G.nz;
-    if (10 * tiles < 11 * n) return kBricksNone;
-  }
+  if (fused_step_bytes(P, mode, n) > brick_bytes_limit(P, mode)) return kBricksNone;
+  const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
+  if (mode != MPLB_CHE_ONLY && bits16 && n > kBrickNodes16 && 10 * march_nodes(G) < 11 * n) return kBricksNone;
   return brick_kind(P, mode, n, 512LL * brick_blocks(G, kBricksMid), 512LL * brick_blocks(G, kBricksWide));
 }
 
-Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[kBrickKinds]) {
-  if (bytes > kBrickBytes) return kBricksNone;
-  if ((P == MPLB_F32_F16 || P == MPLB_F32_BF16) && nodes > kBrickNodes16) return kBricksNone;
-  return brick_kind(P, MPLB_COUPLED, nodes, padded[kBricksMid], padded[kBricksWide]);
+// In a batch, GLUPS in bricks (groups of lattices that fit the cache together)
+// against the marching kernel over many: FP32 32^3 27.1 / 18.9, 48^3 24.4 /
+// 22.0, 64^3 26.3 / 24.7, 96^3 25.4 / 22.2; FP64 32^3 13.6 / 9.1, 48^3 12.8 / 11.2;
+// 16-bit populations 32^3 35.5 / 23.2, 48^3 35.6 / 30.3, 96^3 33.0 / 30.2.  In
+// FP64 and with 16-bit populations a march whose tiles are full is the faster
+// one once its lattices fill the chip: 64^3 11.1 / 12.7 and 32.5 / 38.3.
+BatchUse batch_use(int P, const Geo& G) {
+  const long long n = (long long)G.nx * G.ny * G.nz;
+  if (fused_step_bytes(P, MPLB_COUPLED, n) > kBrickBytes) return kBatchMarch;
+  return P != MPLB_F32 && 10 * march_nodes(G) < 11 * n ? kBatchMarchIfFull : kBatchBricks;
+}
+
+Bricks batch_bricks(int P, long long nodes, long long mid, long long wide) {
+  return brick_kind(P, MPLB_COUPLED, nodes, mid, wide);
 }
 
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br) {

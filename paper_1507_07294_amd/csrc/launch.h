@@ -24,9 +24,13 @@ Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C);
 hipError_t launch_brick_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, Bricks br,
                              hipStream_t s);
 int brick_blocks(const Geo& G, Bricks br);
-// the same for a batch of D3Q15 lattices: `bytes` and `nodes` over the batch,
-// `padded` the nodes that bricks of each kind cover
-Bricks batch_bricks(int P, size_t bytes, long long nodes, const long long padded[kBrickKinds]);
+// The same for lattices that step together: whether a lattice of a batch can
+// and should step in bricks, and the kind for a group of them whose nodes and
+// nodes covered by mid and wide bricks are given.
+enum BatchUse { kBatchMarch = 0, kBatchMarchIfFull = 1, kBatchBricks = 2 };
+BatchUse batch_use(int P, const Geo& G);
+size_t brick_bytes_limit(int P, int mode);
+Bricks batch_bricks(int P, long long nodes, long long mid, long long wide);
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br);
 constexpr int brick_threads(Bricks br) { return br == kBricksNarrow ? 256 : 512; }
 // the kernel and work split of a marching step (host computation only; rows as

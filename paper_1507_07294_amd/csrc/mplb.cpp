@@ -106,6 +106,7 @@ struct mplb_s {
   double velT = 1.0;
   int check_interval = kDefaultCheckInterval;
   int tile_rows = 0;  // mplb_force_tile_rows (0: automatic)
+  int batch_group = 0;  // scratch of mplb_step_many (plan_batch)
   std::string err;
 };
 
@@ -516,27 +517,132 @@ static int check_after(mplb_t* const* hs, int count, int nsteps) {
   return rc;
 }
 
+// A batch steps in groups of lattices that share one launch per step: `count`
+// items of the batch table from `first` on.  A group of one lattice (alone)
+// takes the launch it takes by itself and has no table item.
+struct BatchGroup {
+  BatchForm form;
+  int first, count, blocks;
+  bool alone;
+};
+
+// Steps in a call from which a batch is split into groups whose state stays in
+// the last-level cache, each group doing all its steps before the next (its
+// first step comes from HBM).  Lattices of the serving sizes, us per step in
+// one launch against groups: 24 in FP32 (15 M nodes) 680 / 621 over 8 steps, 683
+// / 586 over 50; 40 with 16-bit populations (25 M) 706 / 736 over 8, 708 / 710
+// over 50, and 24 of them 467 / 426 over 50.
+constexpr int group_steps(int P) { return P == MPLB_F32_F16 || P == MPLB_F32_BF16 ? 32 : 8; }
+// Bytes that the steps of a group move (its state is a little less): lattices
+// 48^3 in FP32, GLUPS, 23.9 in groups of 177 MB and 18.4 in groups of 285 MB;
+// with 16-bit populations 34.4 at 205 MB, 28.9 at 285 MB.
+constexpr size_t kGroupBytes = 205000000;
+// Nodes from which marching lattices with full tiles fill the chip (batch_use):
+// eight of 64^3 (2.1 M) take 72 us per step marching and 62 in bricks with
+// 16-bit populations, 177 and 190 in FP64.
+constexpr long long march_fill(int P) { return P == MPLB_F64 ? 2000000 : 3000000; }
+// Up to two marching lattices step alone, each with the launch it takes by
+// itself (two of 96^3 in FP64: 248 us per step together, 178 one by one; from
+// three on together is as fast or faster).
+constexpr int kMarchTogether = 3;
+
+// Splits a batch into groups (at most `count`, written to out), each lattice's
+// group in its batch_group.
+static int plan_batch(mplb_t* const* hs, int count, int nsteps, bool unit, BatchGroup* out) {
+  const int P = hs[0]->prec;
+  auto bytes_of = [&](int i) { return fused_step_bytes(P, MPLB_COUPLED, hs[i]->G.N); };
+  size_t total = 0;
+  long long marching = 0;
+  for (int i = 0; i < count; ++i) {
+    total += bytes_of(i);
+    if (batch_use(P, hs[i]->G) != kBatchBricks) marching += hs[i]->G.N;
+  }
+  const bool split = nsteps >= group_steps(P) || total <= kGroupBytes;
+  const BatchUse least = marching < march_fill(P) ? kBatchMarchIfFull : kBatchBricks;
+  int marches = 0;
+  for (int i = 0; i < count; ++i) marches += !split || batch_use(P, hs[i]->G) < least;
+  int ng = 0, march = -1, open = -1;  // open: the brick group that still has room
+  size_t used = 0;
+  long long nodes = 0, mid = 0, wide = 0;
+  for (int i = 0; i < count; ++i) {
+    const Geo& G = hs[i]->G;
+    const bool bricks = split && batch_use(P, G) >= least;
+    int g = bricks ? open : march;
+    const bool fresh = g < 0 || (bricks ? used + bytes_of(i) > kGroupBytes : split && marches < kMarchTogether);
+    if (fresh) {
+      g = ng++;
+      out[g] = BatchGroup{{bricks ? kBricksNarrow : kBricksNone, false, false, unit}, 0, 0, 0, false};
+    }
+    if (bricks) {
+      if (fresh) used = 0, nodes = mid = wide = 0;
+      open = g;
+      used += bytes_of(i);
+      nodes += G.N;
+      mid += (long long)brick_threads(kBricksMid) * brick_blocks(G, kBricksMid);
+      wide += (long long)brick_threads(kBricksWide) * brick_blocks(G, kBricksWide);
+      out[g].form.bricks = batch_bricks(P, nodes, mid, wide);
+    } else {
+      march = g;
+    }
+    out[g].form.wall = out[g].form.wall || G.wall_x || G.wall_y || (bricks && G.wall_z);
+    hs[i]->batch_group = g;
+    ++out[g].count;
+  }
+  size_t march_bytes = 0;
+  for (int i = 0; i < count; ++i)
+    if (hs[i]->batch_group == march) march_bytes += bytes_of(i);
+  if (march >= 0) out[march].form.nt = march_bytes > fused_stream_threshold();
+  int first = 0;
+  for (int g = 0; g < ng; ++g) {
+    out[g].alone = split && out[g].count == 1;
+    out[g].first = first;
+    if (!out[g].alone) first += out[g].count;
+  }
+  return ng;
+}
+
 // Upload of a batch table without allocating: items are written into a stack
 // buffer and copied in pieces.  The copies are from pageable memory, so each
 // returns only once its bytes have left the buffer.
-static int upload_table_noalloc(mplb_t* const* hs, int count, Bricks br, void* dtab, hipStream_t s, int* blocks_out) {
+static int upload_table_noalloc(mplb_t* const* hs, int count, BatchGroup* groups, int ng, void* dtab, hipStream_t s) {
   mplb_t* h0 = hs[0];
   const size_t item = fused_batch_item_bytes(h0->prec);
   alignas(64) unsigned char stage[16384];
   const int per = (int)(sizeof stage / item);
   if (per < 1) return fail(h0, MPLB_E_INVAL, "batch item larger than its staging");
-  int blocks = 0;
-  for (int first = 0; first < count; first += per) {
-    const int n = count - first < per ? count - first : per;
-    for (int j = 0; j < n; ++j) {
-      mplb_t* h = hs[first + j];
-      int nb = fused_batch_fill(h->prec, stage, j, h->G, h->C, h->B, h->cur, blocks, br);
+  int done = 0, staged = 0;
+  auto flush = [&]() {
+    hipError_t e = hipMemcpyAsync((char*)dtab + (size_t)done * item, stage, (size_t)staged * item,
+                                  hipMemcpyHostToDevice, s);
+    done += staged;
+    staged = 0;
+    return e;
+  };
+  for (int g = 0; g < ng; ++g) {
+    if (groups[g].alone) continue;
+    for (int i = 0; i < count; ++i) {
+      mplb_t* h = hs[i];
+      if (h->batch_group != g) continue;
+      int nb = fused_batch_fill(h->prec, stage, staged, h->G, h->C, h->B, h->cur, groups[g].blocks,
+                                groups[g].form.bricks);
       if (nb <= 0) return fail(h0, MPLB_E_INVAL, "bad batch item");
-      blocks += nb;
+      groups[g].blocks += nb;
+      if (++staged == per) HIPCHK(h0, flush());
     }
-    HIPCHK(h0, hipMemcpyAsync((char*)dtab + (size_t)first * item, stage, (size_t)n * item, hipMemcpyHostToDevice, s));
   }
-  *blocks_out = blocks;
+  if (staged > 0) HIPCHK(h0, flush());
+  return MPLB_OK;
+}
+
+// nsteps steps of each group that has table items, one group after the other.
+static int launch_groups(mplb_t* h0, const BatchGroup* groups, int ng, const void* dtab, int nsteps, hipStream_t s) {
+  const size_t item = fused_batch_item_bytes(h0->prec);
+  for (int g = 0; g < ng; ++g) {
+    if (groups[g].alone) continue;
+    const void* tab = (const char*)dtab + (size_t)groups[g].first * item;
+    for (int k = 0; k < nsteps; ++k)
+      HIPCHK(h0, launch_fused_many(h0->prec, groups[g].form, tab, groups[g].count, groups[g].blocks, k & 1, s));
+  }
   return MPLB_OK;
 }
 
@@ -571,8 +677,9 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   // that mixes unit and other S^g rates (two collision forms) step one after
   // another: the batched kernel is the default D3Q15 step in one form
   if (h0->mode != MPLB_COUPLED || any_switch || mixed_rates) {
-    for (int k = 0; k < nsteps; ++k)
-      for (int i = 0; i < count; ++i) {
+    // (all steps of one, then of the next: its state stays in the cache)
+    for (int i = 0; i < count; ++i)
+      for (int k = 0; k < nsteps; ++k) {
         int rc = enqueue_step(hs[i], s);
         if (rc) return rc;
       }
@@ -581,34 +688,23 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   int dev = 0;
   HIPCHK(h0, hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(h0, MPLB_E_DEVICE, "device index out of range");
-  bool xywall = false, zwall = false;
-  size_t step_bytes = 0;
-  long long nodes = 0, padded[kBrickKinds] = {};
-  for (int i = 0; i < count; ++i) {
-    const Geo& G = hs[i]->G;
-    xywall = xywall || G.wall_x || G.wall_y;
-    zwall = zwall || G.wall_z;
-    step_bytes += fused_step_bytes(hs[i]->prec, hs[i]->mode, G.N);
-    nodes += G.N;
-    for (Bricks br : {kBricksNarrow, kBricksMid, kBricksWide})
-      padded[br] += (long long)brick_threads(br) * brick_blocks(G, br);
-  }
-  BatchForm form{};
-  form.bricks = batch_bricks(h0->prec, step_bytes, nodes, padded);
-  form.wall = xywall || (form.bricks != kBricksNone && zwall);
-  form.nt = form.bricks == kBricksNone && step_bytes > fused_stream_threshold();
-  form.unit = unit;
-  if (noalloc) {
+  BatchGroup fixed[MPLB_NOALLOC_MAX_LATTICES];
+  std::vector<BatchGroup> grown;
+  if (count > MPLB_NOALLOC_MAX_LATTICES) grown.resize((size_t)count);  // never with noalloc
+  BatchGroup* groups = grown.empty() ? fixed : grown.data();
+  const int ng = plan_batch(hs, count, nsteps, unit, groups);
+  int items = 0;  // lattices with a table item
+  for (int g = 0; g < ng; ++g)
+    if (!groups[g].alone) items += groups[g].count;
+  if (items > 0 && noalloc) {
     void* dtab = nullptr;
     HIPCHK(h0, noalloc_table(dev, &dtab));
-    int blocks = 0;
-    int rc = upload_table_noalloc(hs, count, form.bricks, dtab, s, &blocks);
+    int rc = upload_table_noalloc(hs, count, groups, ng, dtab, s);
+    if (rc == MPLB_OK) rc = launch_groups(h0, groups, ng, dtab, nsteps, s);
     if (rc) return rc;
-    for (int k = 0; k < nsteps; ++k)
-      HIPCHK(h0, launch_fused_many(h0->prec, form, dtab, count, blocks, k & 1, s));
-  } else {
+  } else if (items > 0) {
     BatchTable& T = g_tables[dev];
-    size_t bytes = fused_batch_item_bytes(h0->prec) * (size_t)count;
+    size_t bytes = fused_batch_item_bytes(h0->prec) * (size_t)items;
     if (T.uploaded) HIPCHK(h0, hipEventSynchronize(T.uploaded));  // staging free again
     if (!T.uploaded) HIPCHK(h0, hipEventCreateWithFlags(&T.uploaded, hipEventDisableTiming));
     if (!T.done) HIPCHK(h0, hipEventCreateWithFlags(&T.done, hipEventDisableTiming));
@@ -629,30 +725,46 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
       HIPCHK(h0, hipMalloc(&T.dev, 2 * bytes));
       T.dev_cap = 2 * bytes;
     }
-    int blocks = 0;
-    for (int i = 0; i < count; ++i) {
-      mplb_t* h = hs[i];
-      int nb = fused_batch_fill(h->prec, T.host, i, h->G, h->C, h->B, h->cur, blocks, form.bricks);
-      if (nb <= 0) return fail(h0, MPLB_E_INVAL, "bad batch item");
-      blocks += nb;
+    for (int g = 0; g < ng; ++g) {
+      if (groups[g].alone) continue;
+      int at = groups[g].first;
+      for (int i = 0; i < count; ++i) {
+        mplb_t* h = hs[i];
+        if (h->batch_group != g) continue;
+        int nb = fused_batch_fill(h->prec, T.host, at++, h->G, h->C, h->B, h->cur, groups[g].blocks,
+                                  groups[g].form.bricks);
+        if (nb <= 0) return fail(h0, MPLB_E_INVAL, "bad batch item");
+        groups[g].blocks += nb;
+      }
     }
     // the previous batched launches (perhaps on another stream) still read the table
     HIPCHK(h0, hipStreamWaitEvent(s, T.done, 0));
     HIPCHK(h0, hipMemcpyAsync(T.dev, T.host, bytes, hipMemcpyHostToDevice, s));
     HIPCHK(h0, hipEventRecord(T.uploaded, s));
-    if (g_use_graphs && nsteps > 1) {
+    // one group: a graph, cached while the batch keeps its shape.  Several: their
+    // launches are long enough to hide the next one's, and a graph of all of
+    // them would cost more to build than it saves.
+    int rc = MPLB_OK;
+    if (g_use_graphs && nsteps > 1 && ng == 1) {
       hipGraphExec_t ex = nullptr;
-      int rc = chunk_graph(h0, T, form, count, blocks, nsteps, &ex);
+      rc = chunk_graph(h0, T, groups[0].form, groups[0].count, groups[0].blocks, nsteps, &ex);
       if (rc) return rc;
       HIPCHK(h0, hipGraphLaunch(ex, s));
     } else {
-      for (int k = 0; k < nsteps; ++k)
-        HIPCHK(h0, launch_fused_many(h0->prec, form, T.dev, count, blocks, k & 1, s));
+      rc = launch_groups(h0, groups, ng, T.dev, nsteps, s);
+      if (rc) return rc;
     }
     HIPCHK(h0, hipEventRecord(T.done, s));
   }
   for (int i = 0; i < count; ++i) {
     mplb_t* h = hs[i];
+    if (groups[h->batch_group].alone) {
+      for (int k = 0; k < nsteps; ++k) {
+        int rc = enqueue_step(h, s);
+        if (rc) return rc;
+      }
+      continue;
+    }
     h->step += nsteps;
     if (nsteps & 1) h->cur = 1 - h->cur;
   }

@@ -64,3 +64,32 @@ def test_small_batches_equal_their_lattices_alone(precision):
                 for k in alone:
                     assert np.array_equal(b.read(k), alone[k], equal_nan=True), (precision, unit, w.shape, w.bc, k)
                 b.destroy()
+
+
+def _droplet(shape, seed, bc=(0, 0, 0)):
+    w = wl.static_droplet(n=8)
+    w.shape, w.bc = shape, bc
+    w.phi0 = wl.droplet_phi(*shape, 0.25 * min(shape) + seed, 4.0)
+    return w
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("precision,steps", [("f32", 9), ("f16", 33), ("f64", 8)])
+def test_batches_in_groups_equal_their_lattices_alone(precision, steps, noalloc):
+    """Batches too large for the cache, whose lattices step in several groups:
+    brick groups that fill up, lattices too large for bricks (one, which steps
+    alone, and three, which march together), small ones between them."""
+    big = (136, 130, 100)
+    for sizes in ([(96, 96, 96), (33, 20, 17), (96, 96, 90), big, (20, 9, 40), (96, 40, 64)],
+                  [big, (33, 20, 17), big, (96, 96, 96), (64, 64, 64), big]):
+        ws = [_droplet(s, i, (0, 0, i % 2)) for i, s in enumerate(sizes)]
+        batch = [mplb.from_workload(w, precision) for w in ws]
+        (mplb.mplb_step_many_noalloc if noalloc else mplb.mplb_step_many)(batch, steps)
+        for w, b in zip(ws, batch):
+            lt = mplb.from_workload(w, precision)
+            lt.step(steps)
+            assert b.step_count == lt.step_count == steps
+            for k in ("phi", "uz"):
+                assert np.array_equal(b.read(k), lt.read(k)), (precision, w.shape, k)
+            lt.destroy()
+            b.destroy()
