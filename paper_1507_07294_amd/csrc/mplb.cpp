@@ -1,12 +1,17 @@
 // Host side of libmplb: the C-ABI declared in include/mplb.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "common.h"
@@ -107,6 +112,7 @@ struct mplb_s {
   int check_interval = kDefaultCheckInterval;
   int tile_rows = 0;  // mplb_force_tile_rows (0: automatic)
   int batch_group = 0;  // scratch of mplb_step_many (plan_batch)
+  bool counted = false;  // among the lattices that keep the staging buffers
   std::string err;
 };
 
@@ -120,6 +126,134 @@ static int fail(mplb_t* h, int code, const char* fmt, ...) {
     h->err = buf;
   }
   return code;
+}
+
+// Pinned staging of device-to-host copies.  A copy into the caller's pageable
+// memory goes through the runtime at about 9 GB/s, its page faults included;
+// in chunks through pinned memory it runs at the link's rate, and copying the
+// chunks out on several threads spreads the page faults.  One field of a
+// 256 x 256 x 1024 box (537 MB) 54 -> 16 ms, of 128 x 128 x 512 6.8 -> 2.9 ms,
+// of 256^3 13.1 -> 3.9 ms.
+struct Staging {
+  static constexpr int kSlots = 8;
+  static constexpr size_t kSlotBytes = (size_t)4 << 20;
+  int dev = -1;
+  char* mem = nullptr;
+  hipEvent_t arrived[kSlots] = {};
+  bool busy = false;
+};
+// Up to kPool of them live, whatever their device; a copy that finds none free
+// takes the runtime's path.  They are freed with the last lattice.
+constexpr int kPool = 4;
+static Staging g_staging[kPool];
+static int g_lattices = 0;
+static std::mutex g_staging_mutex;
+
+static void free_staging(Staging& st) {
+  for (auto& e : st.arrived) {
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
+  }
+  if (st.mem) (void)hipHostFree(st.mem);
+  st.mem = nullptr;
+  st.dev = -1;
+}
+
+static void count_lattice(int change) {
+  std::lock_guard<std::mutex> lock(g_staging_mutex);
+  g_lattices += change;
+  if (g_lattices == 0)
+    for (auto& st : g_staging)
+      if (!st.busy) free_staging(st);
+}
+
+// A staging buffer of device `dev`, or nullptr.
+static Staging* take_staging(int dev) {
+  std::lock_guard<std::mutex> lock(g_staging_mutex);
+  Staging* spare = nullptr;
+  for (auto& st : g_staging) {
+    if (st.busy) continue;
+    if (st.mem && st.dev == dev) {
+      st.busy = true;
+      return &st;
+    }
+    if (!spare || !st.mem) spare = &st;
+  }
+  if (!spare) return nullptr;
+  free_staging(*spare);
+  bool ok = hipHostMalloc((void**)&spare->mem, Staging::kSlots * Staging::kSlotBytes, hipHostMallocDefault) == hipSuccess;
+  for (auto& e : spare->arrived) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    free_staging(*spare);
+    return nullptr;
+  }
+  spare->dev = dev;
+  spare->busy = true;
+  return spare;
+}
+
+static void give_staging(Staging* st) {
+  std::lock_guard<std::mutex> lock(g_staging_mutex);
+  st->busy = false;
+  if (g_lattices == 0) free_staging(*st);
+}
+
+// Copies from which several threads copy the chunks out, and their number (a
+// divisor of kSlots, so that a slot stays with one thread).
+constexpr size_t kThreadedCopy = (size_t)16 << 20;
+constexpr int kCopyThreads = 4;
+static_assert(Staging::kSlots % kCopyThreads == 0, "each slot belongs to one thread");
+
+// Device bytes to host memory on stream s; returns once they have arrived.
+static hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  Staging* st = bytes ? take_staging(dev) : nullptr;
+  if (!st) {
+    e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  }
+  const int threads = bytes >= kThreadedCopy ? kCopyThreads : 1;
+  const size_t chunk = threads > 1 ? Staging::kSlotBytes : (size_t)1 << 20;
+  const size_t chunks = (bytes + chunk - 1) / chunk;
+  auto issue = [&](size_t c) {
+    const int slot = (int)(c % Staging::kSlots);
+    const size_t at = c * chunk, len = std::min(chunk, bytes - at);
+    hipError_t r = hipMemcpyAsync(st->mem + slot * Staging::kSlotBytes, (const char*)src + at, len,
+                                  hipMemcpyDeviceToHost, s);
+    return r == hipSuccess ? hipEventRecord(st->arrived[slot], s) : r;
+  };
+  for (size_t c = 0; c < chunks && c < (size_t)Staging::kSlots && e == hipSuccess; ++c) e = issue(c);
+  std::atomic<int> bad{(int)e};
+  // thread t of n takes chunks t, t + n, ...: it copies a chunk out and then
+  // reuses its slot for a later one
+  auto work = [&](int t, int n) {
+    hipError_t r = hipSetDevice(dev);
+    for (size_t c = (size_t)t; c < chunks && r == hipSuccess && bad.load() == (int)hipSuccess; c += (size_t)n) {
+      const int slot = (int)(c % Staging::kSlots);
+      r = hipEventSynchronize(st->arrived[slot]);
+      if (r != hipSuccess) break;
+      const size_t at = c * chunk;
+      std::memcpy((char*)dst + at, st->mem + slot * Staging::kSlotBytes, std::min(chunk, bytes - at));
+      if (c + Staging::kSlots < chunks) r = issue(c + Staging::kSlots);
+    }
+    if (r != hipSuccess) bad.store((int)r);
+  };
+  std::thread helper[kCopyThreads];
+  int started = 1;
+  try {
+    for (; started < threads; ++started) helper[started] = std::thread(work, started, threads);
+  } catch (const std::system_error&) {
+    // fewer threads than wanted: this one does the others' chunks below
+  }
+  work(0, threads);
+  for (int t = started; t < threads; ++t) work(t, threads);
+  for (int t = 1; t < started; ++t) helper[t].join();
+  e = hipStreamSynchronize(s);  // nothing of a failed copy still writes to the slots
+  give_staging(st);
+  return bad.load() != (int)hipSuccess ? (hipError_t)bad.load() : e;
 }
 
 #define HIPCHK(h, expr)                                                                      \
@@ -204,12 +338,15 @@ int mplb_create(int nx, int ny, int nz, const int bc[3], int precision, int mode
     mplb_destroy(h);
     return MPLB_E_DEVICE;
   }
+  h->counted = true;
+  count_lattice(1);
   *out = h;
   return MPLB_OK;
 }
 
 void mplb_destroy(mplb_t* h) {
   if (!h) return;
+  if (h->counted) count_lattice(-1);
   if (h->own_arena && h->arena) {
     (void)hipStreamSynchronize(h->stream);
     (void)hipFree(h->arena);
@@ -796,8 +933,7 @@ int mplb_read(mplb_t* h, int field, double* out) {
   int rc = prepare_macro(h);
   if (rc) return rc;
   HIPCHK(h, launch_macro(h->prec, h->mode, h->G, h->C, h->B, h->cur, field, h->stream));
-  HIPCHK(h, hipMemcpyAsync(out, h->B.out, (size_t)h->G.N * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, copy_out(out, h->B.out, (size_t)h->G.N * sizeof(double), h->stream));
   return MPLB_OK;
 }
 
@@ -818,8 +954,7 @@ int mplb_read_diagonal(mplb_t* h, int field, double* out) {
     HIPCHK(h, launch_diag(h->B.out, d, h->G.nx, h->G.nz, h->stream));
     src = d;
   }
-  HIPCHK(h, hipMemcpyAsync(out, src, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, copy_out(out, src, n * sizeof(double), h->stream));
   return MPLB_OK;
 }
 
@@ -862,12 +997,11 @@ int mplb_checkpoint(mplb_t* h, void* host_buf, size_t bytes) {
   char* p = (char*)host_buf;
   std::memcpy(p, &hd, sizeof hd);
   p += sizeof hd;
-  HIPCHK(h, hipMemcpyAsync(p, h->B.f[h->cur], h->plan.f, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, copy_out(p, h->B.f[h->cur], h->plan.f, h->stream));
   p += h->plan.f;
-  if (h->plan.g) HIPCHK(h, hipMemcpyAsync(p, h->B.g[h->cur], h->plan.g, hipMemcpyDeviceToHost, h->stream));
+  if (h->plan.g) HIPCHK(h, copy_out(p, h->B.g[h->cur], h->plan.g, h->stream));
   p += h->plan.g;
-  HIPCHK(h, hipMemcpyAsync(p, h->B.phiu, h->plan.phiu, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, copy_out(p, h->B.phiu, h->plan.phiu, h->stream));
   return MPLB_OK;
 }
 
