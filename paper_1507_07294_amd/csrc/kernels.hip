@@ -13,6 +13,8 @@
 //   k_phi, k_mu   phi = sum_i f_i (Eq. 13) and mu (Eqs. 2, 36) into arrays,
 //                 for read-out, totals and the initial state
 //   k_macro       one macroscopic field at the current level
+//   k_phi_out     the same for phi and rho, which need the f alone
+//   k_mu_out      the same for mu of the coupled model, from its array
 //   k_totals      FP64 sums of phi, momentum and force, non-finite count
 //   k_front       lowest and highest zero crossing of phi along z
 //   k_init        equilibrium initial state (Eqs. 5, 21)
@@ -63,10 +65,11 @@ __global__ void __launch_bounds__(kBlock) k_mu(Geo G, Coef<typename Prec<P>::T> 
 
 
 // Macroscopic state of node n at the current level (phi and mu arrays must
-// hold this level).  Returns false if a pulled population is non-finite.
+// hold this level), and the pulled g of a coupled model.  Returns false if a
+// pulled population is non-finite.
 template <int P, bool COUPLED, int Q = 15>
 __device__ inline bool node_macro(const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur, int n,
-                                  Macro<typename Prec<P>::T>& M) {
+                                  Macro<typename Prec<P>::T>& M, typename Prec<P>::T g[Q]) {
   using T = typename Prec<P>::T;
   int x, y, z;
   decode(G, n, x, y, z);
@@ -76,7 +79,6 @@ __device__ inline bool node_macro(const Geo& G, const Coef<typename Prec<P>::T>&
   T phi = phi_of(f);
   bool ok = all_finite(f, 7);
   if (COUPLED) {
-    T g[Q];
     pull_g<P, PK, Q>(G, B.f[cur], B.g[cur], x, y, z, n, g);
     ok = ok && all_finite(g, Q);
     const T* mus = (const T*)B.mu;
@@ -105,7 +107,8 @@ __global__ void __launch_bounds__(kBlock) k_macro(Geo G, Coef<typename Prec<P>::
   int n = blockIdx.x * kBlock + threadIdx.x;
   if (n >= G.N) return;
   Macro<T> M;
-  node_macro<P, COUPLED, Q>(G, C, B, cur, n, M);
+  T g[Q];
+  node_macro<P, COUPLED, Q>(G, C, B, cur, n, M, g);
   T v = 0;
   switch (field) {
     case MPLB_PHI: v = M.phi; break;
@@ -117,6 +120,27 @@ __global__ void __launch_bounds__(kBlock) k_macro(Geo G, Coef<typename Prec<P>::
     case MPLB_P: v = M.p; break;
   }
   B.out[n] = (double)v;
+}
+
+// phi (Eq. 13) or rho (Eq. 14) at the current level, from the pulled f alone:
+// one pass instead of the three that the other fields take (phi, mu, field).
+template <int P, bool COUPLED, int Q = 15>
+__global__ void __launch_bounds__(kBlock) k_phi_out(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur, int field) {
+  using T = typename Prec<P>::T;
+  int n = blockIdx.x * kBlock + threadIdx.x;
+  if (n >= G.N) return;
+  int x, y, z;
+  decode(G, n, x, y, z);
+  T f[7];
+  pull_f<P, packed_q<P, COUPLED, Q>()>(G, B.f[cur], x, y, z, n, f);
+  const T phi = phi_of(f);
+  B.out[n] = (double)(field == MPLB_PHI ? phi : (1 + phi) / 2 * C.rho_l + (1 - phi) / 2 * C.rho_g);
+}
+
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_mu_out(Geo G, Bufs B) {
+  int n = blockIdx.x * kBlock + threadIdx.x;
+  if (n < G.N) B.out[n] = (double)((const T*)B.mu)[n];
 }
 
 __device__ inline double wave_sum(double v) {
@@ -135,13 +159,10 @@ __global__ void __launch_bounds__(kBlock) k_totals(Geo G, Coef<typename Prec<P>:
   for (long long nl = (long long)blockIdx.x * kBlock + threadIdx.x; nl < G.N; nl += (long long)gridDim.x * kBlock) {
     const int n = (int)nl;
     Macro<T> M;
-    bool ok = node_macro<P, COUPLED, Q>(G, C, B, cur, n, M);
+    T g[Q];
+    bool ok = node_macro<P, COUPLED, Q>(G, C, B, cur, n, M, g);
     acc[0] += (double)M.phi;
     if (COUPLED) {
-      int x, y, z;
-      decode(G, n, x, y, z);
-      T g[Q];
-      pull_g<P, packed_q<P, COUPLED, Q>(), Q>(G, B.f[cur], B.g[cur], x, y, z, n, g);
       double gd[Q];
       for (int i = 0; i < Q; ++i) gd[i] = (double)g[i];
       for (int i = 0; i < Q; ++i) {
@@ -190,19 +211,25 @@ __global__ void __launch_bounds__(kBlock) k_totals_final(double* red, int nslots
 }
 
 // Interface extremes along z (Rayleigh-Taylor spike tip and bubble front):
-// each thread scans columns (x, y) upward through the phi array, locating
-// sign changes of phi between layers k and k+1 by linear interpolation at
-// z = k + 1/2 + phi_k / (phi_k - phi_{k+1}) (layer k sits at k + 1/2); the
-// block keeps the lowest and highest crossing in slots 0 and 1 of its 8.
+// each thread scans runs of kFrontRun layers of a column (x, y) upward through
+// the phi array, locating sign changes of phi between layers k and k+1 by
+// linear interpolation at z = k + 1/2 + phi_k / (phi_k - phi_{k+1}) (layer k
+// sits at k + 1/2); the block keeps the lowest and highest crossing in slots 0
+// and 1 of its 8.  Whole columns left a 128 x 128 x 512 box with 64 blocks and
+// 512 loads in a row per thread: 232 -> 108 us with the phi pass.
+constexpr int kFrontRun = 16;
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_front(Geo G, Bufs B) {
   const T* phi = (const T*)B.phi;
-  const int cols = G.nx * G.ny;
-  const size_t plane = (size_t)cols;
+  const size_t plane = (size_t)G.nx * G.ny;
+  const int runs = (G.nz - 1 + kFrontRun - 1) / kFrontRun;
   double lo = INFINITY, hi = -INFINITY;
-  for (int c = blockIdx.x * kBlock + threadIdx.x; c < cols; c += gridDim.x * kBlock) {
-    double a = (double)phi[c];
-    for (int k = 0; k + 1 < G.nz; ++k) {
+  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < (long long)plane * runs;
+       i += (long long)gridDim.x * kBlock) {
+    const size_t c = (size_t)(i % (long long)plane);
+    const int k0 = (int)(i / (long long)plane) * kFrontRun, k1 = min(k0 + kFrontRun, G.nz - 1);
+    double a = (double)phi[(size_t)k0 * plane + c];
+    for (int k = k0; k < k1; ++k) {
       const double b = (double)phi[(size_t)(k + 1) * plane + c];
       if ((a < 0.0) != (b < 0.0)) {
         const double z = k + 0.5 + a / (a - b);
@@ -392,6 +419,16 @@ hipError_t macro_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs
 }
 
 template <int P>
+hipError_t phi_out_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs& B, int cur, int field, hipStream_t s) {
+  const auto C = cast_coef<typename Prec<P>::T>(Cd);
+  if (mode == MPLB_COUPLED) hipLaunchKernelGGL((k_phi_out<P, true>), grid_for(G.N), dim3(kBlock), 0, s, G, C, B, cur, field);
+  else if (mode == MPLB_COUPLED_Q19)
+    hipLaunchKernelGGL((k_phi_out<P, true, 19>), grid_for(G.N), dim3(kBlock), 0, s, G, C, B, cur, field);
+  else hipLaunchKernelGGL((k_phi_out<P, false>), grid_for(G.N), dim3(kBlock), 0, s, G, C, B, cur, field);
+  return hipGetLastError();
+}
+
+template <int P>
 hipError_t totals_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs& B, int cur, hipStream_t s) {
   using T = typename Prec<P>::T;
   Coef<T> C = cast_coef<T>(Cd);
@@ -447,6 +484,17 @@ hipError_t launch_mu(int P, const Geo& G, const Coef<double>& Cd, const Bufs& B,
   })
 }
 
+hipError_t launch_phi_out(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, int field,
+                          hipStream_t s) {
+  MPLB_DISPATCH(P, return phi_out_impl<PP>(mode, G, C, B, cur, field, s))
+}
+
+hipError_t launch_mu_out(int P, const Geo& G, const Bufs& B, hipStream_t s) {
+  if (P == MPLB_F64) hipLaunchKernelGGL(k_mu_out<double>, grid_for(G.N), dim3(kBlock), 0, s, G, B);
+  else hipLaunchKernelGGL(k_mu_out<float>, grid_for(G.N), dim3(kBlock), 0, s, G, B);
+  return hipGetLastError();
+}
+
 hipError_t launch_macro(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, int field,
                         hipStream_t s) {
   MPLB_DISPATCH(P, return macro_impl<PP>(mode, G, C, B, cur, field, s))
@@ -457,9 +505,9 @@ hipError_t launch_totals(int P, int mode, const Geo& G, const Coef<double>& C, c
 }
 
 hipError_t launch_front(int P, const Geo& G, const Bufs& B, hipStream_t s) {
-  const int cols = G.nx * G.ny;
-  int blocks = (cols + kBlock - 1) / kBlock;
-  if (blocks > kRedSlots) blocks = kRedSlots;
+  const long long runs = (G.nz - 1 + kFrontRun - 1) / kFrontRun, work = (long long)G.nx * G.ny * runs;
+  const long long want = (work + kBlock - 1) / kBlock;
+  const int blocks = (int)(want < 1 ? 1 : want > kRedSlots ? kRedSlots : want);
   if (P == MPLB_F64) hipLaunchKernelGGL(k_front<double>, dim3(blocks), dim3(kBlock), 0, s, G, B);
   else hipLaunchKernelGGL(k_front<float>, dim3(blocks), dim3(kBlock), 0, s, G, B);
   hipError_t e = hipGetLastError();

@@ -75,6 +75,11 @@ size_t fused_stream_threshold();
 // field (MPLB_PHI..MPLB_P) at the current level into B.out (double)
 hipError_t launch_macro(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                         int field, hipStream_t s);
+// phi or rho at the current level into B.out, from the populations alone; mu of
+// a coupled lattice into B.out, from the B.mu array
+hipError_t launch_phi_out(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, int field,
+                          hipStream_t s);
+hipError_t launch_mu_out(int P, const Geo& G, const Bufs& B, hipStream_t s);
 // FP64 totals and non-finite count into B.red[kRedSlots*8 .. +8)
 hipError_t launch_totals(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                          hipStream_t s);
