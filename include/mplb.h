@@ -156,7 +156,10 @@ int mplb_init(mplb_t* h, const double* phi0, const double* u0);
 
 /* Advance nsteps >= 0 time steps (Eqs. 15-16 and their D3Q15 analogue; the
  * finite differences of Eqs. 34-36).  Returns MPLB_E_NONFINITE if the
- * non-finite check (see mplb_set_check_interval) finds a NaN or Inf. */
+ * non-finite check (see mplb_set_check_interval) finds a NaN or Inf.
+ * Large periodic CHE-only lattices in FP32 compute step two levels per launch
+ * where four steps or more are due before the next check; the fields are
+ * bitwise those of single steps. */
 int mplb_step(mplb_t* h, int nsteps);
 
 /* Every k steps (k >= 1; 1000 for a new lattice) mplb_step and
@@ -254,7 +257,8 @@ int mplb_restore(mplb_t* h, const void* host_buf, size_t bytes);
  * stream around each step kernel; ms[2] and ms[3] receive the summed
  * duration of the step kernels (one kernel does the whole step), ms[0] and
  * ms[1] (separate phi and mu passes, which the step does not have) are 0.
- * Synchronises; the state advances exactly as with mplb_step. */
+ * Times single steps.  Synchronises; the state advances exactly as with
+ * mplb_step. */
 int mplb_time_stages(mplb_t* h, int nsteps, double ms[4]);
 
 /* Measurement reference: copy `bytes` (a multiple of 16) from device buffer
@@ -292,7 +296,7 @@ int mplb_poison(mplb_t* h);
  * compute (any storage) the kernel in which a thread owns two nodes of a
  * 128 x 8 tile on a lattice of at least 5 million nodes that fills at least
  * 384 of those; 8 otherwise.
- * 8 or 16 forces that march (16 where it exists, else MPLB_E_INVAL).  The
+ * 8 or 16 forces that march, one step per launch (16 where it exists, else MPLB_E_INVAL).  The
  * kernel and the tiling change which work a block does, not the arithmetic of
  * a node, so the fields are bitwise the same; mplb_step_many uses 8 rows, or
  * bricks for a batch that is small as a whole. */

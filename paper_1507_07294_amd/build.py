@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmplb.so")
 SOURCES = ["kernels.hip", "fused.hip", "mplb.cpp"]
-HEADERS = ["common.h", "device.h", "launch.h", "brick.h"]
+HEADERS = ["common.h", "device.h", "launch.h", "brick.h", "che_pair.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -135,16 +135,6 @@ __device__ inline void fill_axes(const Geo& G, int x0, int y0, int z0, Axis* tab
   }
 }
 
-// f of one position as stored: f_0 in r0, f_1..f_6 in r (PACK: words that
-// carry g_1..g_6 in their high halves).
-template <int P, bool PACK>
-struct Raw7 {
-  using L = Lat<P, PACK>;
-  using QS = typename std::conditional<PACK, uint32_t, typename L::S>::type;
-  typename L::S0 r0;
-  QS r[6];
-};
-
 // Offsets of the pulls along the axes: o[i - 1] for population i = 1..6.
 __device__ inline void face_offsets(const Axis& x, const Axis& y, const Axis& z, uint32_t o[6]) {
   const uint32_t xy = x.at + y.at, yz = y.at + z.at, xz = x.at + z.at;
@@ -159,27 +149,15 @@ __device__ inline void face_offsets(const Axis& x, const Axis& y, const Axis& z,
 // rf: the f buffer from its start, ri: from the arrays of f_1..f_6
 template <int P, bool PACK>
 __device__ inline void pull7(__amdgpu_buffer_rsrc_t rf, __amdgpu_buffer_rsrc_t ri, uint32_t pitch, const Axis& x,
-                             const Axis& y, const Axis& z, Raw7<P, PACK>& o) {
+                             const Axis& y, const Axis& z, F7Raw<P, PACK>& o) {
   using S0 = typename Lat<P, PACK>::S0;
-  using QS = typename Raw7<P, PACK>::QS;
+  using QS = typename F7Raw<P, PACK>::QS;
   static_assert(sizeof(S0) % sizeof(QS) == 0, "f_0 at a multiple of the others' offset");
   o.r0 = ld_off<S0>(rf, (x.at + y.at + z.at) * (uint32_t)(sizeof(S0) / sizeof(QS)), 0);
   uint32_t off[6];
   face_offsets(x, y, z, off);
 #pragma unroll
   for (int i = 0; i < 6; ++i) o.r[i] = ld_off<QS>(ri, off[i], (uint32_t)(i / 2) * 2 * pitch * (uint32_t)sizeof(QS));
-}
-
-template <int P, bool PACK>
-__device__ inline void cvt7(const Raw7<P, PACK>& o, typename Prec<P>::T f[7]) {
-  using L = Lat<P, PACK>;
-  using T = typename Prec<P>::T;
-  f[0] = (T)o.r0;
-#pragma unroll
-  for (int i = 1; i < 7; ++i) {
-    if constexpr (PACK) f[i] = L::lo(o.r[i - 1]);
-    else f[i] = (T)o.r[i - 1];
-  }
 }
 
 // The g of the brick's own node (PACK: g_0 and g_7 on, at half the offsets of
@@ -190,7 +168,7 @@ __device__ inline void pull_own_g(__amdgpu_buffer_rsrc_t rg, uint32_t pitch, con
                                   const Axis& z, typename Lat<P, PACK>::S g[Q]) {
   using L = Lat<P, PACK>;
   using S = typename L::S;
-  using QS = typename Raw7<P, PACK>::QS;
+  using QS = typename F7Raw<P, PACK>::QS;
   constexpr uint32_t half = sizeof(QS) / sizeof(S);
   const uint32_t arr = pitch * (uint32_t)sizeof(S), next = pitch * (uint32_t)sizeof(QS);
   const uint32_t n = x.at + y.at + z.at;
@@ -241,7 +219,7 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   using L = Lat<P, PACK>;
   using S = typename L::S;
   using S0 = typename L::S0;
-  using QS = typename Raw7<P, PACK>::QS;
+  using QS = typename F7Raw<P, PACK>::QS;
   using D = Pad<BX, BY, BZ, 2>;
   using M1 = Pad<BX, BY, BZ, 1>;
   constexpr int NT = D::NT;
@@ -277,9 +255,9 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   // 16.8 us).
   const Axis ax = tab[tx + 2], ay = tab[D::PX + ty + 2], az = tab[D::PX + D::PY + tz + 2];
   const uint32_t n = ax.at + ay.at + az.at;
-  Raw7<P, PACK> fr;
+  F7Raw<P, PACK> fr;
   pull7<P, PACK>(rf, ri, pitch, ax, ay, az, fr);
-  Raw7<P, PACK> hr[D::HPT];
+  F7Raw<P, PACK> hr[D::HPT];
   int hat[D::HPT];
 #pragma unroll
   for (int k = 0; k < D::HPT; ++k) {
@@ -298,7 +276,7 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
 
   // phi of the padded brick
   T f[7];
-  cvt7<P, PACK>(fr, f);
+  cvt_f7<P, PACK>(fr, f);
   const T phi = phi_of(f);
   const int pat = (tx + 2) + D::PX * (ty + 2) + D::PXY * (tz + 2);
   sphi[pat] = phi;
@@ -306,7 +284,7 @@ __device__ inline void brick_body(const Geo& G, const Coef<typename Prec<P>::T>&
   for (int k = 0; k < D::HPT; ++k) {
     if (tid + k * NT < D::NHALO) {
       T fh[7];
-      cvt7<P, PACK>(hr[k], fh);
+      cvt_f7<P, PACK>(hr[k], fh);
       sphi[hat[k]] = phi_of(fh);
     }
   }
@@ -420,9 +398,9 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   const Axis ax = tab[tx + 1], ay = tab[D::PX + ty + 1], az = tab[D::PX + D::PY + tz + 1];
   const uint32_t n = ax.at + ay.at + az.at;                       // f_1..f_6
   const uint32_t n0 = n * (uint32_t)(sizeof(T) / sizeof(S));      // f_0 and the history
-  Raw7<P, false> fr;
+  F7Raw<P, false> fr;
   pull7<P, false>(rf, ri, pitch, ax, ay, az, fr);
-  Raw7<P, false> hr[D::HPT];
+  F7Raw<P, false> hr[D::HPT];
   int hat[D::HPT];
 #pragma unroll
   for (int k = 0; k < D::HPT; ++k) {
@@ -451,7 +429,7 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
     sn[w][k] = w ? sin(2 * pi * h) : sin(pi * h);
   }
   T f[7];
-  cvt7<P, false>(fr, f);
+  cvt_f7<P, false>(fr, f);
   const T phi = phi_of(f);
   const int pat = (tx + 1) + D::PX * (ty + 1) + D::PXY * (tz + 1);
   sphi[pat] = phi;
@@ -459,7 +437,7 @@ k_brick_che(Geo G, Coef<typename Prec<P>::T> C, Bufs B, int cur) {
   for (int k = 0; k < D::HPT; ++k) {
     if (hat[k] >= 0) {
       T fh[7];
-      cvt7<P, false>(hr[k], fh);
+      cvt_f7<P, false>(hr[k], fh);
       sphi[hat[k]] = phi_of(fh);
     }
   }
@@ -616,8 +594,10 @@ size_t brick_bytes_limit(int P, int mode) {
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
   if (C.stencil7 || C.forcing28) return kBricksNone;  // the study variants are marching kernels
   const long long n = (long long)G.nx * G.ny * G.nz;
-  if (fused_step_bytes(P, mode, n) > brick_bytes_limit(P, mode)) return kBricksNone;
   const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
+  // (a CHE-only node with 16-bit populations: f_0 in 32 bits, six in 16, phi)
+  const size_t bytes = mode == MPLB_CHE_ONLY && bits16 ? (size_t)n * 40 : fused_step_bytes(P, mode, n);
+  if (bytes > brick_bytes_limit(P, mode)) return kBricksNone;
   if (mode != MPLB_CHE_ONLY && bits16 && n > kBrickNodes16 && 10 * march_nodes(G) < 11 * n) return kBricksNone;
   return brick_kind(P, mode, n, 512LL * brick_blocks(G, kBricksMid), 512LL * brick_blocks(G, kBricksWide));
 }

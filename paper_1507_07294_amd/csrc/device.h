@@ -2,11 +2,12 @@
 // access, pull streaming with bounce-back, the finite differences of
 // Eqs. 35-36, the macroscopic closure (Eqs. 29-30), the two moment-space
 // collisions, and the parts that the step kernels share (block order, axis
-// wrapping, buffer resources, the same differences on planes held in LDS).
+// wrapping, pulls by plane, the same differences on planes held in LDS).
 // Included by the kernel translation units.
 #pragma once
 
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 
@@ -614,9 +615,155 @@ __device__ inline int map_axis(int v, int n, int wall) {
 __device__ inline int clamp_axis(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
 __device__ inline int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
+// Source offsets of one lattice column (x, y): for a velocity component c in
+// {-1, 0, 1}, xs[c+1] is the source x (x - c, wrapped) and xb[c+1] says the
+// population comes through an x wall; ys holds y * nx likewise.
+struct Column {
+  int xs[3], ys[3];
+  bool xb[3], yb[3];
+};
+
+template <bool XYWALL>
+__device__ inline Column make_column(const Geo& G, int x, int y) {
+  Column c;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    int sx = x - (k - 1), sy = y - (k - 1);
+    c.xb[k] = XYWALL && G.wall_x && (sx < 0 || sx >= G.nx);
+    c.yb[k] = XYWALL && G.wall_y && (sy < 0 || sy >= G.ny);
+    c.xs[k] = wrap1(sx, G.nx);
+    c.ys[k] = wrap1(sy, G.ny) * G.nx;
+  }
+  return c;
+}
+
+// Plane offsets for the sources of plane z (z - cz) and the z-wall bounce,
+// uniform over the block.
+struct Plane {
+  int zs[3];
+  bool zb[3];
+  int z;
+};
+
+__device__ inline Plane make_plane(const Geo& G, int z) {
+  Plane p;
+  p.z = z;
+  const int nxy = G.nx * G.ny;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    int sz = z - (k - 1);
+    p.zb[k] = G.wall_z && (sz < 0 || sz >= G.nz);
+    p.zs[k] = wrap1(sz, G.nz) * nxy;
+  }
+  return p;
+}
+
+// Pulls into node (column c, plane p).  The bounce-back choice selects an
+// array and an index and then issues one load, so that no load sits behind a
+// branch and all of them are in flight together; with walls on z only the
+// array choice is uniform over the block.
+template <bool XYWALL>
+__device__ inline bool bounced(const Column& c, const Plane& p, int cx, int cy, int cz) {
+  bool b = p.zb[cz + 1];
+  if (XYWALL) b = b || c.xb[cx + 1] || c.yb[cy + 1];
+  return b;
+}
+__device__ inline int source(const Column& c, const Plane& p, int cx, int cy, int cz) {
+  return p.zs[cz + 1] + c.ys[cy + 1] + c.xs[cx + 1];
+}
+
+// Plane-relative addressing.  Every pull of a node reads one z plane per
+// velocity, and which plane (and, on a z wall, which array) is uniform over
+// the block; so a load is a raw buffer access whose resource holds a scalar
+// base (array start plus plane offset, 64-bit scalar arithmetic) and whose
+// lane offset is the 32-bit in-plane byte offset: one vector instruction of
+// address arithmetic per access.  The in-plane byte offset holds while
+// nx*ny*8 < 2^32 (checked when a lattice is created).  The base must be
+// uniform over the wave.
+template <class S>
+__device__ inline const S* plane_base(const void* arr0, size_t arr, int pitch, int zoff) {
+  return (const S*)arr0 + (arr * (size_t)pitch + (size_t)zoff);
+}
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_at(const void* base) {
   // no stride, full 32-bit range, untyped 32-bit data (gfx9 descriptor word 3)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, -1, 0x00020000);
+}
+// NTL: non-temporal load (cache-policy bit 1), for data that no other block
+// reads again.
+template <class S, bool NTL = false>
+__device__ inline S ld_at(const S* base, int xy) {
+  const uint32_t off = (uint32_t)xy * (uint32_t)sizeof(S);
+  constexpr int aux = NTL ? 2 : 0;
+  if constexpr (sizeof(S) == 2) {
+    return __builtin_bit_cast(S, (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc_at(base), off, 0, aux));
+  } else if constexpr (sizeof(S) == 4) {
+    return __builtin_bit_cast(S, (unsigned int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_at(base), off, 0, aux));
+  } else {
+    static_assert(sizeof(S) == 8, "2, 4 or 8 bytes");
+    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(rsrc_at(base), off, 0, aux));
+  }
+}
+// NT: non-temporal (streaming) store, cache-policy bit 1.  It pays when a
+// step's traffic is far larger than the last-level cache; for a lattice that
+// stays resident there it makes the next step's reads go to HBM.
+template <bool NT, class S>
+__device__ inline void st_at(S* base, int xy, S v) {
+  const uint32_t off = (uint32_t)xy * (uint32_t)sizeof(S);
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(S) == 2) {
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), rsrc_at(base), off, 0, aux);
+  } else if constexpr (sizeof(S) == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc_at(base), off, 0, aux);
+  } else {
+    using U2 = unsigned int __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), rsrc_at(base), off, 0, aux);
+  }
+}
+
+// The seven f of the node at in-plane index xy of the plane p (plane offset
+// zo), as stored: f_0 in r0, f_1..f_6 in r (PACK: 32-bit words that carry
+// g_1..g_6 in their high halves).
+template <int P, bool PACK>
+struct F7Raw {
+  using L = Lat<P, PACK>;
+  using QS = typename std::conditional<PACK, uint32_t, typename L::S>::type;
+  typename L::S0 r0;
+  QS r[6];
+};
+
+template <int P, bool PACK, bool XYWALL>
+__device__ inline void pull_f7_raw(const Geo& G, const void* fb, const Column& c, const Plane& p, int zo, int xy,
+                                   F7Raw<P, PACK>& o) {
+  using L = Lat<P, PACK>;
+  using QS = typename F7Raw<P, PACK>::QS;
+  o.r0 = ld_at(L::f0(fb) + zo, xy);
+  const QS* fi = (const QS*)L::fi(fb, G.pitch);
+#pragma unroll
+  for (int i = 1; i < 7; ++i) {
+    const int cx = c7(i, 0), cy = c7(i, 1), cz = c7(i, 2);
+    if constexpr (XYWALL) {
+      const bool b = bounced<XYWALL>(c, p, cx, cy, cz);
+      const int idx = b ? zo + xy : source(c, p, cx, cy, cz);
+      o.r[i - 1] = fi[(size_t)((b ? opp(i) : i) - 1) * G.pitch + idx];
+    } else {
+      // z-wall bounce is uniform: pick array and plane on the scalar side
+      const bool b = p.zb[cz + 1];
+      const QS* base = plane_base<QS>(fi, (size_t)((b ? opp(i) : i) - 1), G.pitch, b ? zo : p.zs[cz + 1]);
+      o.r[i - 1] = ld_at(base, b ? xy : c.ys[cy + 1] + c.xs[cx + 1]);
+    }
+  }
+}
+
+template <int P, bool PACK>
+__device__ inline void cvt_f7(const F7Raw<P, PACK>& o, typename Prec<P>::T f[7]) {
+  using L = Lat<P, PACK>;
+  using T = typename Prec<P>::T;
+  f[0] = (T)o.r0;
+#pragma unroll
+  for (int i = 1; i < 7; ++i) {
+    if constexpr (PACK) f[i] = L::lo(o.r[i - 1]);
+    else f[i] = (T)o.r[i - 1];
+  }
 }
 
 // Eq. 36 at a ring position c of the middle plane pc, with the planes below

@@ -8,8 +8,8 @@
 // population, `pitch` elements apart.
 //
 // The time step itself is one kernel: a march (fused.hip) or, for small
-// lattices, three-dimensional bricks (brick.h, compiled here).  This file holds
-// the per-node kernels around it:
+// lattices, three-dimensional bricks (brick.h, compiled here, as is che_pair.h,
+// two CHE-only steps at once).  This file holds the per-node kernels around it:
 //   k_phi, k_mu   phi = sum_i f_i (Eq. 13) and mu (Eqs. 2, 36) into arrays,
 //                 for read-out, totals and the initial state
 //   k_macro       one macroscopic field at the current level
@@ -24,6 +24,7 @@
 #include "device.h"
 #include "launch.h"
 #include "brick.h"
+#include "che_pair.h"
 
 namespace mplb {
 namespace {

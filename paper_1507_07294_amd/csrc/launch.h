@@ -17,6 +17,13 @@ hipError_t launch_mu(int P, const Geo& G, const Coef<double>& C, const Bufs& B, 
 // FP32 populations only)
 hipError_t launch_fused_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                              hipStream_t s, int rows = 0);
+// Two CHE-only steps at once (che_pair.h), for the lattices that che_pair_fits
+// accepts: ct_next is the time factor of the prescribed velocity of the second
+// step.  Reads buffer `cur` and the phi history in B.phiu, writes buffer
+// 1 - cur and the history of the second step into B.phi: the caller swaps both.
+bool che_pair_fits(int P, int mode, const Geo& G, const Coef<double>& C);
+hipError_t launch_che_pair(int P, const Geo& G, const Coef<double>& C, double ct_next, const Bufs& B, int cur,
+                           hipStream_t s);
 // The same step in three-dimensional bricks, one thread per node (brick.hip),
 // for the lattices that step_bricks picks.
 enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksMid = 2, kBricksWide = 3, kBrickKinds = 4 };

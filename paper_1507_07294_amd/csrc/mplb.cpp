@@ -512,11 +512,33 @@ static int enqueue_step(mplb_t* h, hipStream_t s) {
   return MPLB_OK;
 }
 
+// Enqueue one step, or two pairs of steps where `most` allows them and the
+// lattice takes pairs; *taken receives the number.  A pair leaves the state in
+// the other population buffer and the history in the other array; after two
+// the state lies where four single steps leave it, so a sequence of steps that
+// a caller captured into a graph may be replayed as before.
+static int enqueue_steps(mplb_t* h, int most, hipStream_t s, int* taken) {
+  *taken = 1;
+  if (most < 4 || h->tile_rows != 0 || !che_pair_fits(h->prec, h->mode, h->G, h->C)) return enqueue_step(h, s);
+  *taken = 4;
+  for (int i = 0; i < 2; ++i) {
+    set_vel_time(h);
+    const double ct_next = h->C.vel_kind == MPLB_VEL_DEFORM ? deform_ct(h, h->step + 1) : 1.0;
+    HIPCHK(h, launch_che_pair(h->prec, h->G, h->C, ct_next, h->B, h->cur, s));
+    h->cur = 1 - h->cur;
+    std::swap(h->B.phiu, h->B.phi);  // both hold one value per node
+    h->step += 2;
+  }
+  return MPLB_OK;
+}
+
 int mplb_step(mplb_t* h, int nsteps) {
   if (!h || nsteps < 0) return MPLB_E_INVAL;
   if (!h->have_init) return fail(h, MPLB_E_STATE, "step before init");
-  for (int k = 0; k < nsteps; ++k) {
-    int rc = enqueue_step(h, h->stream);
+  for (int left = nsteps, taken = 0; left > 0; left -= taken) {
+    // pairs do not step over a due check
+    const int check = h->check_interval, due = check > 0 ? check - (int)(h->step % check) : left;
+    int rc = enqueue_steps(h, std::min(left, due), h->stream, &taken);
     if (rc) return rc;
     if (h->check_interval > 0 && h->step % h->check_interval == 0) {
       rc = check_flag(h);
@@ -818,8 +840,8 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   if (h0->mode != MPLB_COUPLED || any_switch || mixed_rates) {
     // (all steps of one, then of the next: its state stays in the cache)
     for (int i = 0; i < count; ++i)
-      for (int k = 0; k < nsteps; ++k) {
-        int rc = enqueue_step(hs[i], s);
+      for (int left = nsteps, taken = 0; left > 0; left -= taken) {
+        int rc = enqueue_steps(hs[i], left, s, &taken);
         if (rc) return rc;
       }
     return check_after(hs, count, nsteps);
