@@ -580,7 +580,25 @@ long long march_nodes(const Geo& G) {
   return (long long)((G.nx + 63) / 64 * 64) * ((G.ny + 7) / 8 * 8) * G.nz;
 }
 
+// A flat lattice, of a node or five along z, say, leaves part of every brick
+// empty.  Bricks are still the faster on a small one, which latency bounds; the
+// march is on a large one, or in a batch of many: where the nodes that bricks
+// cover, times the excess over those that marching tiles do, pass this limit
+// (a lattice counts from an excess of 0.3 on).  us per step, march / bricks,
+// by that product: FP32 256 x 256 (0.8 M) 11.1 / 10.2, 512 x 512 (3.1 M) 18.9 /
+// 22.8, 256 x 256 x 5 (0.3 M) 27.5 / 19.6, 512 x 512 x 5 (1.3 M) 53.9 / 61.1;
+// 24 together, 64 x 64 x 9 (0.4 M) 50 / 36, 64 x 64 (1.2 M) 12.5 / 13.7, 128 x
+// 128 x 5 (1.9 M) 89 / 95; FP64, 64 x 64 x 5 (0.5 M) 48 / 51.
+constexpr long long kFlatWork = 1000000, kFlatWorkBatchF64 = 450000;
+
 }  // namespace
+
+long long flat_work(const Geo& G) {
+  const long long bricks = 512LL * brick_blocks(G, kBricksMid), march = march_nodes(G);
+  return 10 * bricks > 13 * march ? (long long)((double)bricks * (bricks - march) / march) : 0;
+}
+
+long long flat_work_limit(int P) { return P == MPLB_F64 ? kFlatWorkBatchF64 : kFlatWork; }
 
 int brick_blocks(const Geo& G, Bricks br) {
   const int bx = brick_x(br), by = brick_y(br);
@@ -597,7 +615,7 @@ Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
   const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
   // (a CHE-only node with 16-bit populations: f_0 in 32 bits, six in 16, phi)
   const size_t bytes = mode == MPLB_CHE_ONLY && bits16 ? (size_t)n * 40 : fused_step_bytes(P, mode, n);
-  if (bytes > brick_bytes_limit(P, mode)) return kBricksNone;
+  if (bytes > brick_bytes_limit(P, mode) || flat_work(G) > kFlatWork) return kBricksNone;
   if (mode != MPLB_CHE_ONLY && bits16 && n > kBrickNodes16 && 10 * march_nodes(G) < 11 * n) return kBricksNone;
   return brick_kind(P, mode, n, 512LL * brick_blocks(G, kBricksMid), 512LL * brick_blocks(G, kBricksWide));
 }

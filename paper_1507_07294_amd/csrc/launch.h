@@ -36,6 +36,10 @@ int brick_blocks(const Geo& G, Bricks br);
 // nodes covered by mid and wide bricks are given.
 enum BatchUse { kBatchMarch = 0, kBatchMarchIfFull = 1, kBatchBricks = 2 };
 BatchUse batch_use(int P, const Geo& G);
+// Idle work of bricks on a flat lattice (0 for others), and the sum from which
+// a batch's flat lattices march.
+long long flat_work(const Geo& G);
+long long flat_work_limit(int P);
 size_t brick_bytes_limit(int P, int mode);
 Bricks batch_bricks(int P, long long nodes, long long mid, long long wide);
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br);

@@ -713,21 +713,26 @@ static int plan_batch(mplb_t* const* hs, int count, int nsteps, bool unit, Batch
   const int P = hs[0]->prec;
   auto bytes_of = [&](int i) { return fused_step_bytes(P, MPLB_COUPLED, hs[i]->G.N); };
   size_t total = 0;
-  long long marching = 0;
+  long long marching = 0, flat = 0;
   for (int i = 0; i < count; ++i) {
     total += bytes_of(i);
+    flat += flat_work(hs[i]->G);
     if (batch_use(P, hs[i]->G) != kBatchBricks) marching += hs[i]->G.N;
   }
   const bool split = nsteps >= group_steps(P) || total <= kGroupBytes;
   const BatchUse least = marching < march_fill(P) ? kBatchMarchIfFull : kBatchBricks;
+  auto in_bricks = [&](int i) {
+    const Geo& G = hs[i]->G;
+    return split && batch_use(P, G) >= least && !(flat > flat_work_limit(P) && flat_work(G) > 0);
+  };
   int marches = 0;
-  for (int i = 0; i < count; ++i) marches += !split || batch_use(P, hs[i]->G) < least;
+  for (int i = 0; i < count; ++i) marches += !in_bricks(i);
   int ng = 0, march = -1, open = -1;  // open: the brick group that still has room
   size_t used = 0;
   long long nodes = 0, mid = 0, wide = 0;
   for (int i = 0; i < count; ++i) {
     const Geo& G = hs[i]->G;
-    const bool bricks = split && batch_use(P, G) >= least;
+    const bool bricks = in_bricks(i);
     int g = bricks ? open : march;
     const bool fresh = g < 0 || (bricks ? used + bytes_of(i) > kGroupBytes : split && marches < kMarchTogether);
     if (fresh) {

@@ -93,3 +93,19 @@ def test_batches_in_groups_equal_their_lattices_alone(precision, steps, noalloc)
                 assert np.array_equal(b.read(k), lt.read(k)), (precision, w.shape, k)
             lt.destroy()
             b.destroy()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32", "bf16"])
+def test_flat_lattices_equal_the_march(precision):
+    """Lattices of few layers on both sides of the limit from which they march,
+    alone and with a cube in a batch."""
+    for shape, count in (((256, 250, 1), 1), ((512, 510, 1), 1), ((130, 128, 5), 2), ((130, 128, 5), 9)):
+        ws = [_droplet(shape, i, (0, 0, i % 2)) for i in range(count)] + [_droplet((40, 40, 40), 1)]
+        batch = [mplb.from_workload(w, precision) for w in ws]
+        mplb.mplb_step_many(batch, 9)
+        for w, b in zip(ws, batch):
+            for rows in (0, 8):
+                alone = _fields(w, precision, 9, rows, False)
+                for k in alone:
+                    assert np.array_equal(b.read(k), alone[k], equal_nan=True), (precision, w.shape, count, rows, k)
+            b.destroy()
