@@ -23,12 +23,14 @@
 // kernel reads one buffer and writes another, which the host swaps.
 //
 // 64 x 16 with 1024 threads and 158 KB of LDS is the largest tile a CU holds
-// (frames and tile: 1.56 collisions of the first step per node).  What bounds
-// it is the chain of a plane, some 4.2 us per iteration at any size and
-// storage type: VALU work of 16 waves between two barriers, with the next
-// plane's pulls in flight.  256^3 FP32: 153 us per step, 221 in single steps
-// (5.0 TB/s of HBM); FP16 142 against 163.  Two iterations per round of the
-// loop, which saves the copies of the queued planes, spill: 164 us.
+// (1.5 pulls and 1.33 collisions of the first step per node).  What bounds
+// it is the chain of a plane, some 4.1 us per iteration at any size and
+// storage type: the vector work of 16 waves between two barriers, with the next
+// plane's pulls in flight; HBM moves 3.9 TB/s.  256^3 FP32: 144 us per step, 221
+// in single steps (5.0 TB/s); FP16 134 against 163.  One kernel per kind of
+// velocity: with the kinds told apart inside the loop the registers spilled and
+// 256^3 took 153 us.  Two iterations per round of the loop, which saves the
+// copies of the queued planes, spill too: 164 us.
 #pragma once
 
 #include "common.h"
@@ -41,8 +43,31 @@ namespace {
 using namespace dev;
 
 constexpr int kPairCUs = 256, kPairMinLz = 16, kPairRows = 16;
+// more nodes than a plane has (and its bytes fit 32 bits)
+constexpr uint32_t kPairPlane = 0x30000000;
 
-template <int P, bool NT, int TY>
+// v as it would be read back after a store in type S.  The conversion stays
+// here, next to the collision's last multiply-add, which the compiler joins with
+// it into one rounding at the stores of a single step.
+template <class S, class T>
+__device__ inline T rounded(T v) {
+  T r = (T)(S)v;
+  if constexpr (sizeof(S) < sizeof(T)) asm volatile("" : "+v"(r));
+  return r;
+}
+
+// Store into a plane of `bytes` bytes; an offset beyond them drops the store.
+template <bool NT, class S>
+__device__ inline void st_plane(S* base, uint32_t bytes, uint32_t off, S v) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)bytes, 0x00020000);
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(S) == 2)
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, off, 0, aux);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, aux);
+}
+
+template <int P, bool NT, int TY, int VK>
 __global__ void __launch_bounds__(64 * TY) __attribute__((amdgpu_waves_per_eu(waves_per_eu<P>())))
 k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs B, int cur, Tiling TL) {
   using T = typename Prec<P>::T;
@@ -97,15 +122,21 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
   const int lx[2] = {tx, ex}, ly[2] = {ty, ey};
   int xy[2], xm[2], xp[2], ym[2], yp[2];  // in-plane offsets of the node and its neighbours
   int at1[2], at2[2], atf[2];
-  bool on[2], first[2];  // node has phi of level n; node takes the first step
+  // The frame node has phi of level n; takes the first step; has phi of level
+  // n+1.  The tile node has all, also beyond the lattice, where it steps the
+  // node that its position wraps to and stores nothing: every load and store of
+  // the tile is issued by every lane, so that the number in flight is known and
+  // the wait for the pulls is none for the stores behind them.
+  bool on1 = false, first1 = false;
   PrescColumn<T> pc[2];
-  T zy[2];  // y - L/2 of Zalesak's rotation
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int gx = x0 + lx[j], gy = y0 + ly[j];
-    const bool need = gx <= G.nx + 2 && gy <= G.ny + 2;
-    on[j] = need && (j == 0 || tid < E3);
-    first[j] = need && (j == 0 || tid < E2);
+    if (j == 1) {
+      const bool need = gx <= G.nx + 2 && gy <= G.ny + 2;
+      on1 = need && tid < E3;
+      first1 = need && tid < E2;
+    }
     const int mx = map_axis(gx, G.nx, 0), my = map_axis(gy, G.ny, 0);
     xy[j] = mx + G.nx * my;
     xm[j] = wrap1(mx - 1, G.nx) + G.nx * my;
@@ -115,30 +146,32 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
     at1[j] = (lx[j] + 3) + X3 * (ly[j] + 3);
     atf[j] = (lx[j] + 2) + X2 * (ly[j] + 2);
     at2[j] = (lx[j] + 1) + X1 * (ly[j] + 1);
-    pc[j].init(G, C, mx, my);
-    zy[j] = (T)my - (T)G.nx / 2;
+    if (VK == MPLB_VEL_DEFORM) pc[j].init(G, C, mx, my);
+    if (VK == MPLB_VEL_ZALESAK) pc[j].a[0] = (T)my - (T)G.nx / 2;  // y - L/2
   }
   // prescribed velocity of node j in plane z (the i-th of the march) with time
   // factor ct
   auto velocity = [&](int j, int i, int z, T ct, T u[3]) {
     u[0] = u[1] = u[2] = 0;
-    if (C.vel_kind == MPLB_VEL_DEFORM) {
+    if constexpr (VK == MPLB_VEL_DEFORM) {
       const T* sn = sz[i / 64 % 2][i % 64];
       const T s = sn[0], s2z = sn[1];
       const T b[3] = {pc[j].a[0] * s2z, pc[j].a[1] * s2z, pc[j].a[2] * s * s};
 #pragma unroll
       for (int a = 0; a < 3; ++a) u[a] = b[a] * ct;
-    } else if (C.vel_kind == MPLB_VEL_ZALESAK) {
+    } else if constexpr (VK == MPLB_VEL_ZALESAK) {
       const T pi = (T)3.14159265358979323846, len = (T)G.nx;
       u[1] = (C.velU * pi / len) * (len / 2 - (T)z);
-      u[2] = (C.velU * pi / len) * zy[j];
+      u[2] = (C.velU * pi / len) * pc[j].a[0];
     }
   };
 
   F7Raw<P, false> raw[2];    // pulls in flight, plane k+1
   T fp[2][7] = {};           // f of plane k-1
   T c0[2] = {0, 0}, c5[2] = {0, 0}, c5p[2] = {0, 0};  // f*_0 of k-2, f*_5 of k-2 and k-3
+  bool finite = true;        // f of both steps of the tile node's column
   const int nxy = G.nx * G.ny;
+  const uint32_t out = own ? (uint32_t)xy[0] : kPairPlane;  // dropped by st_plane
   // the lattice's planes of k-2 .. k+2, wrapped
   int zk[5];
   for (int i = 0; i < 5; ++i) zk[i] = map_axis(z0 - 5 + i, G.nz, 0);
@@ -150,8 +183,8 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
     const S* f5 = fi + ((size_t)4 * G.pitch + (size_t)below * nxy);
     const S* f6 = fi + ((size_t)5 * G.pitch + (size_t)above * nxy);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (on[j]) {
+    for (int j = 1; j >= 0; --j) {
+      if (j == 0 || on1) {
         raw[j].r0 = ld_at(f0, xy[j]);
         raw[j].r[0] = ld_at(fz, xm[j]);
         raw[j].r[1] = ld_at(fz + (size_t)G.pitch, xp[j]);
@@ -173,13 +206,13 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
     if constexpr (A) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if (on[j]) {
+        if (j == 0 || on1) {
           cvt_f7<P, false>(raw[j], fk[j]);
           s1[t % 6][at1[j]] = phi_of(fk[j]);
         }
       }
       const int run = t - 9;
-      if (C.vel_kind == MPLB_VEL_DEFORM && run % 64 == 0 && tid < 128) {
+      if (VK == MPLB_VEL_DEFORM && __builtin_expect(run % 64 == 0 && tid < 128, 0)) {
         const T pi = (T)3.14159265358979323846;
         const T zh = (T)map_axis(k + tid / 2, G.nz, 0) / (T)G.nz;
         sz[run / 64 % 2][tid / 2][tid % 2] = tid % 2 ? sin(2 * pi * zh) : sin(pi * zh);
@@ -190,46 +223,45 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
     if constexpr (DB) {
       const T* h = hin + (size_t)zk[1] * nxy;
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        if (first[j]) hp[j] = ld_at<T>(h, xy[j]);
+      for (int j = 1; j >= 0; --j)
+        if (j == 0 || first1) hp[j] = ld_at<T>(h, xy[j]);
     }
     if constexpr (NEXT) issue(zk[2], zk[3], zk[4]);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     if constexpr (DD) {
-      if (own) {
-        const int z = k - 4;
-        const size_t zo = (size_t)z * nxy;
-        T fb[7];
+      const int z = k - 4;
+      const size_t zo = (size_t)z * nxy;
+      T fb[7];
 #pragma unroll
-        for (int i = 0; i < 7; ++i) fb[i] = sq[t % 2][i][tid];
-        const T* pm = s2[(t - 5) % 4];
-        const T* pm1 = s2[(t - 4) % 4];
-        const T* pp = s2[(t - 3) % 4];
-        const T phi = phi_of(fb);
-        const T lap = lap_lds<T, X1>(pm, pm1, pp, at2[0]);
-        const T mu = 4 * C.beta * phi * (phi - 1) * (phi + 1) - C.kappa * lap;
-        const T phip = s1[(t - 4) % 6][at1[0]];
-        T u[3], up[3], dphiu[3];
-        velocity(0, t - 13, z, ct_next, u);
-        velocity(0, t - 13, z, C.vel_ct, up);
-        st_at<NT>(hout + zo, xy[0], phi);
+      for (int i = 0; i < 7; ++i) fb[i] = sq[t % 2][i][tid];
+      const T* pm = s2[(t - 5) % 4];
+      const T* pm1 = s2[(t - 4) % 4];
+      const T* pp = s2[(t - 3) % 4];
+      const T phi = phi_of(fb);
+      const T lap = lap_lds<T, X1>(pm, pm1, pp, at2[0]);
+      const T mu = 4 * C.beta * phi * (phi - 1) * (phi + 1) - C.kappa * lap;
+      const T phip = s1[(t - 4) % 6][at1[0]];
+      T u[3], up[3], dphiu[3];
+      velocity(0, t - 13, z, ct_next, u);
+      velocity(0, t - 13, z, C.vel_ct, up);
+      st_plane<NT>(hout + zo, nxy * (uint32_t)sizeof(T), out * (uint32_t)sizeof(T), phi);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) dphiu[a] = __builtin_fmaf(phi, u[a], -(phip * up[a]));
-        collide_che(C, fb, phi, mu, u, dphiu);
-        st_at<NT>(L::f0(fo) + zo, xy[0], (S0)fb[0]);
-        S* fs = L::fi(fo, G.pitch);
+      for (int a = 0; a < 3; ++a) dphiu[a] = __builtin_fmaf(phi, u[a], -(phip * up[a]));
+      collide_che(C, fb, phi, mu, u, dphiu);
+      st_plane<NT>(L::f0(fo) + zo, nxy * (uint32_t)sizeof(S0), out * (uint32_t)sizeof(S0), (S0)fb[0]);
+      S* fs = L::fi(fo, G.pitch);
 #pragma unroll
-        for (int i = 1; i < 7; ++i) st_at<NT>(fs + ((size_t)(i - 1) * G.pitch + zo), xy[0], (S)fb[i]);
-        if (!all_finite(fb, 7)) *B.flag = 1;
-      }
+      for (int i = 1; i < 7; ++i)
+        st_plane<NT>(fs + ((size_t)(i - 1) * G.pitch + zo), nxy * (uint32_t)sizeof(S), out * (uint32_t)sizeof(S), (S)fb[i]);
+      finite = finite && all_finite(fb, 7);
     }
     T c6[2] = {0, 0}, d0[2] = {0, 0}, d5[2] = {0, 0};  // f* of plane k-1
     if constexpr (DB) {
       const int z = zk[1];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if (first[j]) {
+        if (j == 0 || first1) {
           T f[7];
 #pragma unroll
           for (int i = 0; i < 7; ++i) f[i] = fp[j][i];
@@ -242,14 +274,12 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
 #pragma unroll
           for (int a = 0; a < 3; ++a) dphiu[a] = __builtin_fmaf(phi, u[a], -(hp[j] * up[a]));
           collide_che(C, f, phi, mu, u, dphiu);
-          // rounded to the storage type next to the collision, before any branch:
-          // the compiler then rounds once, as at the stores of a single step
-          d0[j] = (T)(S0)f[0];
+          d0[j] = rounded<S0>(f[0]);
 #pragma unroll
-          for (int i = 1; i < 5; ++i) sf[(t - 1) % 2][i - 1][atf[j]] = (T)(S)f[i];
-          d5[j] = (T)(S)f[5];
-          c6[j] = (T)(S)f[6];
-          if (j == 0 && own && !all_finite(f, 7)) *B.flag = 1;
+          for (int i = 1; i < 5; ++i) sf[(t - 1) % 2][i - 1][atf[j]] = rounded<S>(f[i]);
+          d5[j] = rounded<S>(f[5]);
+          c6[j] = rounded<S>(f[6]);
+          if (j == 0) finite = finite && all_finite(f, 7);
         }
       }
     }
@@ -257,7 +287,7 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
       const T(*q)[N2] = sf[t % 2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if (j == 0 ? first[0] : tid < E1) {
+        if (j == 0 || tid < E1) {
           T f[7] = {c0[j], q[0][atf[j] - 1], q[1][atf[j] + 1], q[2][atf[j] - X2], q[3][atf[j] + X2], c5p[j], c6[j]};
           s2[(t - 2) % 4][at2[j]] = phi_of(f);
           if (j == 0) {
@@ -290,6 +320,7 @@ k_che_pair(Geo G, Coef<typename Prec<P>::T> C, typename Prec<P>::T ct_next, Bufs
   for (int k = z0 + 4; k < z1 + 2; ++k) iterate(k, Y, Y, Y, Y, Y);
   iterate(z1 + 2, Y, O, Y, Y, Y);
   iterate(z1 + 3, O, O, O, O, Y);
+  if (own && !finite) *B.flag = 1;
 }
 
 // Work split of the pair.  A CU holds one block at a time and spends about the
@@ -325,8 +356,11 @@ hipError_t pair_impl2(const Geo& G, const Coef<double>& Cd, double ct_next, cons
   using T = typename Prec<P>::T;
   constexpr int TY = kPairRows;
   const Tiling t = pair_plan(G, TY).t;
-  hipLaunchKernelGGL((k_che_pair<P, NT, TY>), dim3((unsigned)(t.tiles_x * t.tiles_y * t.nseg)), dim3(64 * TY), 0, s, G,
-                     cast_coef<T>(Cd), (T)ct_next, B, cur, t);
+  void (*k)(Geo, Coef<T>, T, Bufs, int, Tiling) = k_che_pair<P, NT, TY, MPLB_VEL_ZERO>;
+  if (Cd.vel_kind == MPLB_VEL_ZALESAK) k = k_che_pair<P, NT, TY, MPLB_VEL_ZALESAK>;
+  if (Cd.vel_kind == MPLB_VEL_DEFORM) k = k_che_pair<P, NT, TY, MPLB_VEL_DEFORM>;
+  hipLaunchKernelGGL(k, dim3((unsigned)(t.tiles_x * t.tiles_y * t.nseg)), dim3(64 * TY), 0, s, G, cast_coef<T>(Cd),
+                     (T)ct_next, B, cur, t);
   return hipGetLastError();
 }
 
@@ -345,15 +379,15 @@ hipError_t pair_impl(const Geo& G, const Coef<double>& C, double ct_next, const 
 // Pairs lose where their tiles, segments and rounds leave much idle, so the
 // nodes that they could step are weighed against those that the march's 64 x 8
 // tiles cover.  us per step, single against pairs, by that ratio: FP32 0.91
-// (256^3) 221 / 153, 0.79 (192^3) 116 / 76, 0.70 (200^3) 135 / 128, 0.57
-// (1024 x 1024 x 8) 122 / 108, 0.49 (1000 x 1000 x 6) 98 / 94; 16-bit
+// (256^3) 221 / 144, 0.79 (192^3) 116 / 71, 0.70 (200^3) 135 / 120, 0.57
+// (1024 x 1024 x 8) 122 / 103, 0.49 (1000 x 1000 x 6) 98 / 94; 16-bit
 // populations, whose single step moves 40 bytes per node instead of 64, 0.91
-// 163 / 142, 0.79 (224^3) 130 / 118, 0.74 (400 x 400 x 100) 244 / 187, 0.70
-// (200 x 200 x 220) 130 / 122 but (200^3) 104 / 111, 0.57 96 / 101.
+// 163 / 134, 0.79 (224^3) 130 / 110, 0.74 (400 x 400 x 100) 244 / 174, just
+// below 0.70 (200^3) 104 / 104, 0.57 96 / 96.
 bool che_pair_fits(int P, int mode, const Geo& G, const Coef<double>& C) {
   if (mode != MPLB_CHE_ONLY || G.wall_x || G.wall_y || G.wall_z || C.stencil7 || C.vel_kind == MPLB_VEL_FIELD) return false;
-  if (P == MPLB_F64 || G.nz < 2 || step_bricks(P, mode, G, C) != kBricksNone) return false;
-  return 100 * march_nodes(G) >= (P == MPLB_F32 ? 50 : 72) * pair_plan(G, kPairRows).nodes;
+  if (P == MPLB_F64 || G.nz < 2 || (uint64_t)G.nx * G.ny > kPairPlane || step_bricks(P, mode, G, C) != kBricksNone) return false;
+  return 100 * march_nodes(G) >= (P == MPLB_F32 ? 50 : 70) * pair_plan(G, kPairRows).nodes;
 }
 
 hipError_t launch_che_pair(int P, const Geo& G, const Coef<double>& C, double ct_next, const Bufs& B, int cur,
