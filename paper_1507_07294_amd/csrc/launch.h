@@ -24,7 +24,7 @@ hipError_t launch_fused_step(int P, int mode, const Geo& G, const Coef<double>& 
 bool che_pair_fits(int P, int mode, const Geo& G, const Coef<double>& C);
 hipError_t launch_che_pair(int P, const Geo& G, const Coef<double>& C, double ct_next, const Bufs& B, int cur,
                            hipStream_t s);
-// The same step in three-dimensional bricks, one thread per node (brick.hip),
+// The same step in three-dimensional bricks, one thread per node (brick.h),
 // for the lattices that step_bricks picks.
 enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksMid = 2, kBricksWide = 3, kBrickKinds = 4 };
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C);

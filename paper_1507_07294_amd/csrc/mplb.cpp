@@ -132,8 +132,8 @@ static int fail(mplb_t* h, int code, const char* fmt, ...) {
 // memory goes through the runtime at about 9 GB/s, its page faults included;
 // in chunks through pinned memory it runs at the link's rate, and copying the
 // chunks out on several threads spreads the page faults.  One field of a
-// 256 x 256 x 1024 box (537 MB) 54 -> 16 ms, of 128 x 128 x 512 6.8 -> 2.9 ms,
-// of 256^3 13.1 -> 3.9 ms.
+// 256 x 256 x 1024 box (537 MB) 54 -> 13.5 ms, of 128 x 128 x 512 6.8 -> 2.1 ms,
+// of 256^3 13.1 -> 3.7 ms.
 struct Staging {
   static constexpr int kSlots = 8;
   static constexpr size_t kSlotBytes = (size_t)4 << 20;
