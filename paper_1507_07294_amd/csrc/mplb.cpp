@@ -8,9 +8,9 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -247,8 +247,9 @@ static hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t
   int started = 1;
   try {
     for (; started < threads; ++started) helper[started] = std::thread(work, started, threads);
-  } catch (const std::system_error&) {
-    // fewer threads than wanted: this one does the others' chunks below
+  } catch (const std::exception&) {
+    // no thread or no memory for one (std::system_error, std::bad_alloc): this
+    // thread does the others' chunks below
   }
   work(0, threads);
   for (int t = started; t < threads; ++t) work(t, threads);
