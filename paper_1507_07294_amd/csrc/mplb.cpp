@@ -9,7 +9,9 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
@@ -123,7 +125,11 @@ static int fail(mplb_t* h, int code, const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    h->err = buf;
+    try {
+      h->err = buf;
+    } catch (const std::bad_alloc&) {
+      h->err.clear();  // the code alone says it
+    }
   }
   return code;
 }
@@ -856,9 +862,12 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
   HIPCHK(h0, hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(h0, MPLB_E_DEVICE, "device index out of range");
   BatchGroup fixed[MPLB_NOALLOC_MAX_LATTICES];
-  std::vector<BatchGroup> grown;
-  if (count > MPLB_NOALLOC_MAX_LATTICES) grown.resize((size_t)count);  // never with noalloc
-  BatchGroup* groups = grown.empty() ? fixed : grown.data();
+  std::unique_ptr<BatchGroup[]> grown;
+  if (count > MPLB_NOALLOC_MAX_LATTICES) {  // never with noalloc
+    grown.reset(new (std::nothrow) BatchGroup[(size_t)count]);
+    if (!grown) return fail(h0, MPLB_E_NOMEM, "no host memory for a batch of %d", count);
+  }
+  BatchGroup* groups = grown ? grown.get() : fixed;
   const int ng = plan_batch(hs, count, nsteps, unit, groups);
   int items = 0;  // lattices with a table item
   for (int g = 0; g < ng; ++g)

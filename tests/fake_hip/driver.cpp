@@ -119,11 +119,30 @@ static void copy_without_memory() {
   mplb_destroy(h);
 }
 
+// No memory for the plan of a batch beyond 512 lattices: refused, and nothing
+// has stepped.
+static void batch_without_memory() {
+  const int count = MPLB_NOALLOC_MAX_LATTICES + 1;
+  std::vector<std::vector<char>> arena(count);
+  std::vector<mplb_t*> hs;
+  for (int i = 0; i < count; ++i) hs.push_back(make(2, 2, 2, MPLB_F32, MPLB_COUPLED, arena[i]));
+  no_memory = true;
+  int rc = -1;
+  try {
+    rc = mplb_step_many(hs.data(), count, 3);
+  } catch (const std::bad_alloc&) {
+  }
+  no_memory = false;
+  EXPECT(rc == MPLB_E_NOMEM && mplb_step_count(hs[0]) == 0 && mplb_step_count(hs[count - 1]) == 0);
+  for (mplb_t* h : hs) mplb_destroy(h);
+}
+
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } cases[] = {{"copy_without_memory", copy_without_memory}};
+  } cases[] = {{"copy_without_memory", copy_without_memory},
+               {"batch_without_memory", batch_without_memory}};
   for (const auto& c : cases)
     if (argc == 2 && !std::strcmp(argv[1], c.name)) {
       c.run();
