@@ -213,12 +213,22 @@ constexpr size_t kThreadedCopy = (size_t)6 << 20;
 constexpr int kCopyThreads = 4;
 static_assert(Staging::kSlots % kCopyThreads == 0, "each slot belongs to one thread");
 
+// Whether s is a stream of the current device, whose events are those of the
+// staging buffers.  A caller may read a lattice of another device.
+static bool stream_of_current(hipStream_t s, int dev) {
+  if (!s) return true;
+  hipDevice_t of = -1;
+  if (hipStreamGetDevice(s, &of) == hipSuccess) return of == dev;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Device bytes to host memory on stream s; returns once they have arrived.
 static hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  Staging* st = bytes ? take_staging(dev) : nullptr;
+  Staging* st = bytes && stream_of_current(s, dev) ? take_staging(dev) : nullptr;
   if (!st) {
     e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;

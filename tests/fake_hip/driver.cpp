@@ -36,9 +36,21 @@ void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 // ------------------------------------------------------------ fake HIP
+// Two devices; a stream and an event belong to one, and an event is recorded on
+// its own device's streams only.
+struct FakeStream {
+  int device;
+};
+struct FakeEvent {
+  int device;
+};
+static thread_local int current = 0;
+static int device_of(hipStream_t s) { return s ? ((FakeStream*)s)->device : current; }
+
 extern "C" {
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { current = d; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "fake error"; }
 hipError_t hipMalloc(void** p, size_t n) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
@@ -53,10 +65,17 @@ hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) { std::memset(p
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) {
+  auto* f = (FakeEvent*)std::malloc(sizeof(FakeEvent));
+  f->device = current;
+  *e = (hipEvent_t)f;
+  return hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { std::free((void*)e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  return ((FakeEvent*)e)->device == device_of(s) ? hipSuccess : hipErrorInvalidHandle;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
 static char symbol[1 << 20];
@@ -119,6 +138,20 @@ static void copy_without_memory() {
   mplb_destroy(h);
 }
 
+// A lattice on a stream of another device than the caller's current one.
+static void copy_from_another_device() {
+  FakeStream other{1};
+  for (int n : {8, 100}) {  // alone, and by several threads
+    std::vector<char> arena;
+    mplb_t* h = make(64, 64, n, MPLB_F64, MPLB_CHE_ONLY, arena);
+    EXPECT(mplb_set_stream(h, &other) == MPLB_OK);
+    std::vector<char> out(checkpoint_bytes(h));
+    EXPECT(mplb_checkpoint(h, out.data(), out.size()) == MPLB_OK && checkpoint_matches(arena, out));
+    EXPECT(current == 0);
+    mplb_destroy(h);
+  }
+}
+
 // No memory for the plan of a batch beyond 512 lattices: refused, and nothing
 // has stepped.
 static void batch_without_memory() {
@@ -142,7 +175,8 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } cases[] = {{"copy_without_memory", copy_without_memory},
-               {"batch_without_memory", batch_without_memory}};
+               {"batch_without_memory", batch_without_memory},
+               {"copy_from_another_device", copy_from_another_device}};
   for (const auto& c : cases)
     if (argc == 2 && !std::strcmp(argv[1], c.name)) {
       c.run();

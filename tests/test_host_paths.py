@@ -28,7 +28,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["copy_without_memory", "batch_without_memory"])
+@pytest.mark.parametrize("case", ["copy_without_memory", "batch_without_memory", "copy_from_another_device"])
 def test_host_path(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
