@@ -6,9 +6,13 @@
 //   driver CASE     prints "ok" and exits 0 if every expectation holds
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <future>
 #include <new>
 #include <vector>
 
@@ -45,6 +49,9 @@ struct FakeEvent {
   int device;
 };
 static thread_local int current = 0;
+static std::atomic<int> host_allocations{0}, host_live{0}, events_live{0};
+static int event_limit = 1 << 20;
+static std::function<void()> during_host_malloc;
 static int device_of(hipStream_t s) { return s ? ((FakeStream*)s)->device : current; }
 
 extern "C" {
@@ -55,8 +62,18 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "fake error"; }
 hipError_t hipMalloc(void** p, size_t n) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  if (during_host_malloc) during_host_malloc();
+  ++host_allocations;
+  ++host_live;
+  *p = std::malloc(n);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void* p) {
+  --host_live;
+  std::free(p);
+  return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
   std::memcpy(dst, src, n);
   return hipSuccess;
@@ -66,13 +83,15 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) {
+  if (events_live == event_limit) return hipErrorOutOfMemory;
+  ++events_live;
   auto* f = (FakeEvent*)std::malloc(sizeof(FakeEvent));
   f->device = current;
   *e = (hipEvent_t)f;
   return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t e) { std::free((void*)e); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { --events_live; std::free((void*)e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   return ((FakeEvent*)e)->device == device_of(s) ? hipSuccess : hipErrorInvalidHandle;
 }
@@ -170,13 +189,66 @@ static void batch_without_memory() {
   for (mplb_t* h : hs) mplb_destroy(h);
 }
 
+// Pinned staging is allocated for copies that it speeds up, and goes with the
+// last lattice.
+static void staging_of_short_lives() {
+  std::vector<double> out(60 * 60 * 60);
+  std::vector<char> arena;
+  for (int life = 0; life < 3; ++life) {  // one small lattice at a time, read five times
+    mplb_t* h = make(48, 48, 48, MPLB_F32, MPLB_COUPLED, arena);
+    for (int f = MPLB_PHI; f <= MPLB_UY; ++f) EXPECT(mplb_read(h, f, out.data()) == MPLB_OK);
+    mplb_destroy(h);
+  }
+  EXPECT(host_allocations == 0 && events_live == 0);
+  mplb_t* h = make(60, 60, 60, MPLB_F32, MPLB_COUPLED, arena);
+  for (int f = MPLB_PHI; f <= MPLB_UY; ++f) EXPECT(mplb_read(h, f, out.data()) == MPLB_OK);
+  EXPECT(host_allocations == 1 && host_live == 1);
+  mplb_destroy(h);
+  EXPECT(host_live == 0 && events_live == 0);
+}
+
+// A read that allocates staging holds up no other.
+static void staging_is_allocated_unlocked() {
+  std::vector<char> a, b;
+  mplb_t* large = make(64, 64, 64, MPLB_F32, MPLB_COUPLED, a);
+  mplb_t* small = make(8, 8, 8, MPLB_F32, MPLB_COUPLED, b);
+  std::vector<double> out(64 * 64 * 64), other(8 * 8 * 8);
+  std::future<int> read;
+  bool waited = true;
+  during_host_malloc = [&] {
+    read = std::async(std::launch::async, [&] { return mplb_read(small, MPLB_PHI, other.data()); });
+    waited = read.wait_for(std::chrono::seconds(5)) != std::future_status::ready;
+  };
+  EXPECT(mplb_read(large, MPLB_PHI, out.data()) == MPLB_OK);
+  during_host_malloc = nullptr;
+  EXPECT(!waited && read.get() == MPLB_OK);
+  mplb_destroy(large);
+  mplb_destroy(small);
+  EXPECT(host_live == 0 && events_live == 0);
+}
+
+// Staging that cannot be had whole: the runtime's own copy, and nothing kept.
+static void copy_without_events() {
+  std::vector<char> arena;
+  mplb_t* h = make(64, 64, 100, MPLB_F64, MPLB_CHE_ONLY, arena);
+  std::vector<char> out(checkpoint_bytes(h));
+  event_limit = 2;
+  EXPECT(mplb_checkpoint(h, out.data(), out.size()) == MPLB_OK && checkpoint_matches(arena, out));
+  EXPECT(host_allocations > 0 && events_live <= 2);
+  mplb_destroy(h);
+  EXPECT(host_live == 0 && events_live == 0);
+}
+
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
   } cases[] = {{"copy_without_memory", copy_without_memory},
                {"batch_without_memory", batch_without_memory},
-               {"copy_from_another_device", copy_from_another_device}};
+               {"copy_from_another_device", copy_from_another_device},
+               {"copy_without_events", copy_without_events},
+               {"staging_of_short_lives", staging_of_short_lives},
+               {"staging_is_allocated_unlocked", staging_is_allocated_unlocked}};
   for (const auto& c : cases)
     if (argc == 2 && !std::strcmp(argv[1], c.name)) {
       c.run();
