@@ -246,12 +246,22 @@ static bool stream_of_current(hipStream_t s, int dev) {
   return false;
 }
 
+// Whether p is memory that the runtime knows (page-locked, say): the copy engine
+// writes there at the link's rate without help.
+static bool known_to_runtime(const void* p) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type != hipMemoryTypeUnregistered;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Device bytes to host memory on stream s; returns once they have arrived.
 static hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  Staging* st = bytes >= kStagedCopy && stream_of_current(s, dev) ? take_staging(dev) : nullptr;
+  Staging* st = nullptr;
+  if (bytes >= kStagedCopy && !known_to_runtime(dst) && stream_of_current(s, dev)) st = take_staging(dev);
   if (!st) {
     e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;

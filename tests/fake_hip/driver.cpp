@@ -50,7 +50,9 @@ struct FakeEvent {
 };
 static thread_local int current = 0;
 static std::atomic<int> host_allocations{0}, host_live{0}, events_live{0};
+static std::atomic<int> copies{0};
 static int event_limit = 1 << 20;
+static const void *locked_from = nullptr, *locked_to = nullptr;  // page-locked memory of the caller
 static std::function<void()> during_host_malloc;
 static int device_of(hipStream_t s) { return s ? ((FakeStream*)s)->device : current; }
 
@@ -74,7 +76,15 @@ hipError_t hipHostFree(void* p) {
   std::free(p);
   return hipSuccess;
 }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  const bool locked = p >= locked_from && p < locked_to;
+  if (!locked) return hipErrorInvalidValue;  // what older runtimes say of pageable memory
+  *a = hipPointerAttribute_t{};
+  a->type = hipMemoryTypeHost;
+  return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
+  ++copies;
   std::memcpy(dst, src, n);
   return hipSuccess;
 }
@@ -227,6 +237,19 @@ static void staging_is_allocated_unlocked() {
   EXPECT(host_live == 0 && events_live == 0);
 }
 
+// Into the caller's page-locked memory: one copy per array and no staging.
+static void copy_to_page_locked() {
+  std::vector<char> arena;
+  mplb_t* h = make(64, 64, 100, MPLB_F64, MPLB_CHE_ONLY, arena);  // f and the history
+  std::vector<char> out(checkpoint_bytes(h));
+  locked_from = out.data();
+  locked_to = out.data() + out.size();
+  copies = 0;
+  EXPECT(mplb_checkpoint(h, out.data(), out.size()) == MPLB_OK && checkpoint_matches(arena, out));
+  EXPECT(host_allocations == 0 && copies == 2);
+  mplb_destroy(h);
+}
+
 // Staging that cannot be had whole: the runtime's own copy, and nothing kept.
 static void copy_without_events() {
   std::vector<char> arena;
@@ -247,6 +270,7 @@ int main(int argc, char** argv) {
                {"batch_without_memory", batch_without_memory},
                {"copy_from_another_device", copy_from_another_device},
                {"copy_without_events", copy_without_events},
+               {"copy_to_page_locked", copy_to_page_locked},
                {"staging_of_short_lives", staging_of_short_lives},
                {"staging_is_allocated_unlocked", staging_is_allocated_unlocked}};
   for (const auto& c : cases)
