@@ -296,25 +296,42 @@ int mplb_poison(mplb_t* h);
  * compute (any storage) the kernel in which a thread owns two nodes of a
  * 128 x 8 tile on a lattice of at least 5 million nodes that fills at least
  * 384 of those; 8 otherwise.
- * 8 or 16 forces that march, one step per launch (16 where it exists, else MPLB_E_INVAL).  The
- * kernel and the tiling change which work a block does, not the arithmetic of
- * a node, so the fields are bitwise the same; mplb_step_many uses 8 rows, or
- * bricks for a batch that is small as a whole. */
+ * 8 or 16 forces that march, one step per launch (16 where it exists, else
+ * MPLB_E_INVAL).  The kernel and the tiling change which work a block does, not
+ * the arithmetic of a node, so the fields are bitwise the same.  In a batch that
+ * mplb_step_many advances with shared launches it holds only for a lattice that
+ * such a call steps by itself (mplb_step_many_kinds). */
 int mplb_force_tile_rows(mplb_t* h, int rows);
 
 /* The marching kernel and work split for a lattice of nx*ny*nz nodes in this
- * precision and mode, with `rows` as for mplb_force_tile_rows (0: the
- * automatic choice among the marches; the bricks that mplb_step takes on small
- * lattices instead have no such split and are not reported).  A host computation: it needs no device and no
- * lattice.  out[0]: 0 the coupled step on 64 x 8 tiles, 1 on 64 x 16 tiles,
- * 2 the CHE-only step with one node per thread (64 x 8 tiles), 3 with two
- * nodes per thread (128 x 8 tiles); out[1], out[2]: tile width and height in
- * nodes; out[3]: planes per z segment (the last segment may be shorter);
- * out[4]: segments; out[5]: blocks of the launch (tiles times segments).
- * MPLB_E_INVAL for sizes, modes or precisions mplb_create refuses, or rows
- * that mplb_force_tile_rows refuses.  Every choice gives the same results
- * bit for bit; it sets only the speed of the step. */
+ * precision and mode, with `rows` as for mplb_force_tile_rows (0: the automatic
+ * choice among the marches).  mplb_step runs it where it takes neither bricks
+ * nor pairs of steps: mplb_step_shape says which.  A host computation: it needs
+ * no device and no lattice.  out[0]: 0 the coupled step on 64 x 8 tiles, 1 on
+ * 64 x 16 tiles, 2 the CHE-only step with one node per thread (64 x 8 tiles), 3
+ * with two nodes per thread (128 x 8 tiles); out[1], out[2]: tile width and
+ * height in nodes; out[3]: planes per z segment (the last segment may be
+ * shorter); out[4]: segments; out[5]: blocks of the launch (tiles times
+ * segments).  MPLB_E_INVAL for sizes, modes or precisions mplb_create refuses,
+ * or rows that mplb_force_tile_rows refuses.  Every choice gives the same
+ * results bit for bit; it sets only the speed of the step. */
 int mplb_launch_shape(int nx, int ny, int nz, int precision, int mode, int rows, int out[6]);
+
+/* The kernel and work split that mplb_step launches first when nsteps >= 1
+ * steps are due before the next check, for such a lattice with walls bc, on a
+ * CHE-only lattice the prescribed velocity vel_kind (else MPLB_VEL_ZERO), and
+ * the study switches that are set (bit 0 the stencil, bit 1 the forcing).  Host
+ * computation, out as for mplb_launch_shape; out[0] besides: 4, 5, 6 one step in bricks of 16 x 4 x 4,
+ * 16 x 8 x 4, 32 x 4 x 4 nodes (out[4]: layers of bricks), 7 two CHE-only steps
+ * on 64 x 16 tiles. */
+int mplb_step_shape(int nx, int ny, int nz, const int bc[3], int precision, int mode, int vel_kind, int study,
+                    int rows, int nsteps, int out[6]);
+
+/* For each lattice of a batch, the kernel (out[0] of mplb_step_shape; 0: the
+ * batched march) that mplb_step_many(hs, count, nsteps) first steps it with.
+ * Enqueues nothing; refuses what mplb_step_many refuses, and count or nsteps
+ * below 1.  Not thread-safe with other calls on these lattices. */
+int mplb_step_many_kinds(mplb_t* const* hs, int count, int nsteps, int* kinds);
 
 void mplb_destroy(mplb_t* h);
 const char* mplb_last_error(const mplb_t* h);

@@ -605,6 +605,11 @@ int brick_blocks(const Geo& G, Bricks br) {
   return ((G.nx + bx - 1) / bx) * ((G.ny + by - 1) / by) * ((G.nz + 3) / 4);
 }
 
+Shape brick_shape(const Geo& G, Bricks br) {
+  const int bx = brick_x(br), by = brick_y(br);
+  return Shape{kShapeBricks + (int)br - 1, bx, by, Tiling{(G.nx + bx - 1) / bx, (G.ny + by - 1) / by, 4, (G.nz + 3) / 4}};
+}
+
 size_t brick_bytes_limit(int P, int mode) {
   return mode == MPLB_CHE_ONLY && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes;
 }

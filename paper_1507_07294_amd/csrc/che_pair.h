@@ -390,6 +390,8 @@ bool che_pair_fits(int P, int mode, const Geo& G, const Coef<double>& C) {
   return 100 * march_nodes(G) >= (P == MPLB_F32 ? 50 : 70) * pair_plan(G, kPairRows).nodes;
 }
 
+Shape che_pair_shape(const Geo& G) { return Shape{kShapePair, 64, kPairRows, pair_plan(G, kPairRows).t}; }
+
 hipError_t launch_che_pair(int P, const Geo& G, const Coef<double>& C, double ct_next, const Bufs& B, int cur,
                            hipStream_t s) {
   switch (P) {

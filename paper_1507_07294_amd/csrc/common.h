@@ -68,10 +68,13 @@ struct Tiling {
   int tiles_x, tiles_y, lz, nseg;
 };
 
-// Kernel and work split of one step (launch_shape): the coupled step on
+// Kernel and work split of a step.  Marches (launch_shape): the coupled step on
 // 64 x 8 or 64 x 16 tiles, the CHE-only step with one node per thread (64 x 8)
-// or two (128 x 8).
-enum ShapeKind { kShapeCoupled8 = 0, kShapeCoupled16 = 1, kShapeChe1 = 2, kShapeChe2 = 3 };
+// or two (128 x 8).  Beside them (step_shape): bricks, whose kind is
+// kShapeBricks plus their Bricks value less one and whose segments are their
+// layers, and two CHE-only steps at once.
+enum ShapeKind { kShapeCoupled8 = 0, kShapeCoupled16 = 1, kShapeChe1 = 2, kShapeChe2 = 3, kShapeBricks = 4,
+                 kShapePair = 7 };
 struct Shape {
   int kind, tile_w, tile_h;
   Tiling tl;

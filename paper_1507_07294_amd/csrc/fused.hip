@@ -880,6 +880,12 @@ Shape launch_shape(int P, int mode, const Geo& G, int rows) {
   return Shape{kShapeChe1, kTX, kTY, tl};
 }
 
+Shape step_shape(int P, int mode, const Geo& G, const Coef<double>& C, int rows, bool pairs) {
+  if (rows == 0 && pairs && che_pair_fits(P, mode, G, C)) return che_pair_shape(G);
+  const Bricks br = rows == 0 ? step_bricks(P, mode, G, C) : kBricksNone;
+  return br != kBricksNone ? brick_shape(G, br) : launch_shape(P, mode, G, rows);
+}
+
 namespace {
 
 template <int P, bool XYWALL, bool NT, int V>

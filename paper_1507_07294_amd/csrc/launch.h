@@ -47,6 +47,11 @@ constexpr int brick_threads(Bricks br) { return br == kBricksNarrow ? 256 : 512;
 // the kernel and work split of a marching step (host computation only; rows as
 // for launch_fused_step, assumed valid for P and mode)
 Shape launch_shape(int P, int mode, const Geo& G, int rows);
+// the same for the launches of one step (`pairs` false) or of steps that may go
+// in pairs, whichever kernel runs them
+Shape step_shape(int P, int mode, const Geo& G, const Coef<double>& C, int rows, bool pairs);
+Shape brick_shape(const Geo& G, Bricks br);
+Shape che_pair_shape(const Geo& G);
 // Batched coupled step over a device table of BatchItem<T> (T of P):
 // fused_batch_item_bytes gives the item size, fused_batch_fill writes item i
 // of a host table and returns that lattice's block count, launch_fused_many

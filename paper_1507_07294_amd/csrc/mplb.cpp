@@ -562,6 +562,8 @@ static int enqueue_step(mplb_t* h, hipStream_t s) {
   return MPLB_OK;
 }
 
+constexpr int kPairSteps = 4;  // two pairs
+
 // Enqueue one step, or two pairs of steps where `most` allows them and the
 // lattice takes pairs; *taken receives the number.  A pair leaves the state in
 // the other population buffer and the history in the other array; after two
@@ -569,8 +571,8 @@ static int enqueue_step(mplb_t* h, hipStream_t s) {
 // a caller captured into a graph may be replayed as before.
 static int enqueue_steps(mplb_t* h, int most, hipStream_t s, int* taken) {
   *taken = 1;
-  if (most < 4 || h->tile_rows != 0 || !che_pair_fits(h->prec, h->mode, h->G, h->C)) return enqueue_step(h, s);
-  *taken = 4;
+  if (most < kPairSteps || h->tile_rows != 0 || !che_pair_fits(h->prec, h->mode, h->G, h->C)) return enqueue_step(h, s);
+  *taken = kPairSteps;
   for (int i = 0; i < 2; ++i) {
     set_vel_time(h);
     const double ct_next = h->C.vel_kind == MPLB_VEL_DEFORM ? deform_ct(h, h->step + 1) : 1.0;
@@ -862,13 +864,8 @@ static int launch_groups(mplb_t* h0, const BatchGroup* groups, int ng, const voi
   return MPLB_OK;
 }
 
-// mplb_step_many and its allocation-free variant.
-static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc) {
-  if (!hs || count < 0 || nsteps < 0) return MPLB_E_INVAL;
-  if (count == 0 || nsteps == 0) return MPLB_OK;
-  if (noalloc && count > MPLB_NOALLOC_MAX_LATTICES)
-    return fail(hs[0], MPLB_E_INVAL, "step_many_noalloc: %d lattices exceed its static table of %d", count,
-                MPLB_NOALLOC_MAX_LATTICES);
+// Whether these lattices may step together.
+static int check_batch(mplb_t* const* hs, int count) {
   for (int i = 0; i < count; ++i) {
     if (!hs[i]) return MPLB_E_INVAL;
     if (!hs[i]->have_init) return fail(hs[i], MPLB_E_STATE, "step before init");
@@ -881,18 +878,33 @@ static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc
     for (int j = 0; j < i; ++j)
       if (hs[j] == hs[i]) return fail(hs[0], MPLB_E_INVAL, "a lattice appears twice in step_many");
   }
+  return MPLB_OK;
+}
+
+// CHE-only and D3Q19 lattices, lattices with a study switch, and a batch
+// that mixes unit and other S^g rates (two collision forms) step one after
+// another: the batched kernel is the default D3Q15 step in one form.
+static bool one_by_one(mplb_t* const* hs, int count) {
+  for (int i = 0; i < count; ++i)
+    if (hs[i]->mode != MPLB_COUPLED || hs[i]->C.forcing28 || hs[i]->C.stencil7 ||
+        hs[i]->C.unit_rates != hs[0]->C.unit_rates)
+      return true;
+  return false;
+}
+
+// mplb_step_many and its allocation-free variant.
+static int step_many_impl(mplb_t* const* hs, int count, int nsteps, bool noalloc) {
+  if (!hs || count < 0 || nsteps < 0) return MPLB_E_INVAL;
+  if (count == 0 || nsteps == 0) return MPLB_OK;
+  if (noalloc && count > MPLB_NOALLOC_MAX_LATTICES)
+    return fail(hs[0], MPLB_E_INVAL, "step_many_noalloc: %d lattices exceed its static table of %d", count,
+                MPLB_NOALLOC_MAX_LATTICES);
+  const int bad = check_batch(hs, count);
+  if (bad) return bad;
   mplb_t* h0 = hs[0];
   hipStream_t s = h0->stream;
-  bool any_switch = false, mixed_rates = false;
-  for (int i = 0; i < count; ++i) {
-    any_switch = any_switch || hs[i]->C.forcing28 || hs[i]->C.stencil7;
-    mixed_rates = mixed_rates || hs[i]->C.unit_rates != h0->C.unit_rates;
-  }
   const bool unit = h0->C.unit_rates != 0;
-  // CHE-only and D3Q19 lattices, lattices with a study switch, and a batch
-  // that mixes unit and other S^g rates (two collision forms) step one after
-  // another: the batched kernel is the default D3Q15 step in one form
-  if (h0->mode != MPLB_COUPLED || any_switch || mixed_rates) {
+  if (one_by_one(hs, count)) {
     // (all steps of one, then of the next: its state stays in the cache)
     for (int i = 0; i < count; ++i)
       for (int left = nsteps, taken = 0; left > 0; left -= taken) {
@@ -994,6 +1006,28 @@ int mplb_step_many(mplb_t* const* hs, int count, int nsteps) { return step_many_
 
 int mplb_step_many_noalloc(mplb_t* const* hs, int count, int nsteps) {
   return step_many_impl(hs, count, nsteps, true);
+}
+
+int mplb_step_many_kinds(mplb_t* const* hs, int count, int nsteps, int* kinds) {
+  if (!hs || !kinds || count < 1 || nsteps < 1) return MPLB_E_INVAL;
+  const int bad = check_batch(hs, count);
+  if (bad) return bad;
+  const bool each = one_by_one(hs, count);
+  std::unique_ptr<BatchGroup[]> groups;
+  if (!each) {
+    groups.reset(new (std::nothrow) BatchGroup[(size_t)count]);
+    if (!groups) return fail(hs[0], MPLB_E_NOMEM, "no host memory for a batch of %d", count);
+    plan_batch(hs, count, nsteps, hs[0]->C.unit_rates != 0, groups.get());
+  }
+  for (int i = 0; i < count; ++i) {
+    const mplb_t* h = hs[i];
+    const BatchGroup* g = each ? nullptr : &groups[h->batch_group];
+    if (!g || g->alone)
+      kinds[i] = step_shape(h->prec, h->mode, h->G, h->C, h->tile_rows, each && nsteps >= kPairSteps).kind;
+    else
+      kinds[i] = g->form.bricks == kBricksNone ? kShapeCoupled8 : kShapeBricks + (int)g->form.bricks - 1;
+  }
+  return MPLB_OK;
 }
 
 int mplb_check_finite(mplb_t* h) {
@@ -1127,27 +1161,55 @@ int mplb_copy_probe(const void* src, void* dst, size_t bytes, int kind, void* hi
   return launch_copy_probe(src, dst, bytes, kind, (hipStream_t)hip_stream) == hipSuccess ? MPLB_OK : MPLB_E_DEVICE;
 }
 
-int mplb_launch_shape(int nx, int ny, int nz, int precision, int mode, int rows, int out[6]) {
-  if (!out || !valid_dims(nx, ny, nz) || !valid_mode(mode, precision)) return MPLB_E_INVAL;
-  if (rows != 0 && rows != 8 && rows != 16) return MPLB_E_INVAL;
-  if (rows == 16 && (mode == MPLB_CHE_ONLY ? precision == MPLB_F64 : precision != MPLB_F32)) return MPLB_E_INVAL;
+static bool valid_rows(int rows, int precision, int mode) {
+  if (rows == 16) return mode == MPLB_CHE_ONLY ? precision != MPLB_F64 : precision == MPLB_F32;
+  return rows == 0 || rows == 8;
+}
+
+static Geo geo_of(int nx, int ny, int nz) {
   Geo G{};
   G.nx = nx; G.ny = ny; G.nz = nz;
   G.N = nx * ny * nz;
-  const Shape sh = launch_shape(precision, mode, G, rows);
+  return G;
+}
+
+static void shape_out(const Shape& sh, int out[6]) {
   out[0] = sh.kind;
   out[1] = sh.tile_w;
   out[2] = sh.tile_h;
   out[3] = sh.tl.lz;
   out[4] = sh.tl.nseg;
   out[5] = sh.tl.tiles_x * sh.tl.tiles_y * sh.tl.nseg;
+}
+
+int mplb_launch_shape(int nx, int ny, int nz, int precision, int mode, int rows, int out[6]) {
+  if (!out || !valid_dims(nx, ny, nz) || !valid_mode(mode, precision)) return MPLB_E_INVAL;
+  if (!valid_rows(rows, precision, mode)) return MPLB_E_INVAL;
+  shape_out(launch_shape(precision, mode, geo_of(nx, ny, nz), rows), out);
+  return MPLB_OK;
+}
+
+int mplb_step_shape(int nx, int ny, int nz, const int bc[3], int precision, int mode, int vel_kind, int study,
+                    int rows, int nsteps, int out[6]) {
+  if (!out || !bc || nsteps < 1 || !valid_dims(nx, ny, nz) || !valid_mode(mode, precision)) return MPLB_E_INVAL;
+  if (!valid_rows(rows, precision, mode)) return MPLB_E_INVAL;
+  if (vel_kind < MPLB_VEL_ZERO || vel_kind > MPLB_VEL_DEFORM || study < 0 || study > 3) return MPLB_E_INVAL;
+  for (int a = 0; a < 3; ++a)
+    if (bc[a] != MPLB_PERIODIC && bc[a] != MPLB_WALL) return MPLB_E_INVAL;
+  Geo G = geo_of(nx, ny, nz);
+  G.wall_x = bc[0] == MPLB_WALL; G.wall_y = bc[1] == MPLB_WALL; G.wall_z = bc[2] == MPLB_WALL;
+  Coef<double> C{};
+  C.vel_kind = vel_kind;
+  C.stencil7 = study & 1;
+  C.forcing28 = (study & 2) != 0;
+  shape_out(step_shape(precision, mode, G, C, rows, nsteps >= kPairSteps), out);
   return MPLB_OK;
 }
 
 int mplb_force_tile_rows(mplb_t* h, int rows) {
   if (!h) return MPLB_E_INVAL;
   if (rows != 0 && rows != 8 && rows != 16) return fail(h, MPLB_E_INVAL, "tile rows must be 0, 8 or 16");
-  if (rows == 16 && (h->mode == MPLB_CHE_ONLY ? h->prec == MPLB_F64 : h->prec != MPLB_F32))
+  if (!valid_rows(rows, h->prec, h->mode))
     return fail(h, MPLB_E_INVAL,
                 "16-row tiles exist for the coupled step with FP32 populations and the CHE-only step in FP32 compute");
   h->tile_rows = rows;

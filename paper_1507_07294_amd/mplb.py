@@ -88,6 +88,9 @@ def lib():
             "mplb_poke": (C.c_int, [vp, C.c_int, C.c_int, C.c_long, C.c_double]),
             "mplb_force_tile_rows": (C.c_int, [vp, C.c_int]),
             "mplb_launch_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]),
+            "mplb_step_shape": (C.c_int, [C.c_int, C.c_int, C.c_int, ip, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int,
+                                          C.c_int, ip]),
+            "mplb_step_many_kinds": (C.c_int, [C.POINTER(vp), C.c_int, C.c_int, ip]),
             "mplb_poison": (C.c_int, [vp]),
             "mplb_time_stages": (C.c_int, [vp, C.c_int, dp]),
             "mplb_copy_probe": (C.c_int, [vp, vp, sz, C.c_int, vp]),
@@ -145,18 +148,34 @@ def to_params(p) -> mplb_params:
 
 
 SHAPE_KINDS = ("coupled, 64 x 8 tiles", "coupled, 64 x 16 tiles", "CHE-only, one node per thread",
-               "CHE-only, two nodes per thread")
+               "CHE-only, two nodes per thread", "bricks of 16 x 4 x 4", "bricks of 16 x 8 x 4", "bricks of 32 x 4 x 4",
+               "CHE-only, two steps on 64 x 16 tiles")
+
+
+def _shape_dict(out):
+    return {"kind": out[0], "tile": (out[1], out[2]), "lz": out[3], "segments": out[4], "blocks": out[5]}
 
 
 def mplb_launch_shape(nx, ny, nz, precision, mode, rows=0):
-    """The kernel and work split mplb_step uses for such a lattice (host
+    """The marching kernel and its work split for such a lattice (host
     computation): kind (index into SHAPE_KINDS), tile width and height,
     planes per segment, segments and blocks."""
     out = (C.c_int * 6)()
     rc = lib().mplb_launch_shape(nx, ny, nz, precision, mode, rows, out)
     if rc:
         raise MplbError(rc, "mplb_launch_shape")
-    return {"kind": out[0], "tile": (out[1], out[2]), "lz": out[3], "segments": out[4], "blocks": out[5]}
+    return _shape_dict(out)
+
+
+def mplb_step_shape(nx, ny, nz, bc, precision, mode, velocity="zero", study=0, rows=0, nsteps=1):
+    """The kernel and work split with which mplb_step starts on nsteps steps of
+    such a lattice (host computation), as mplb_launch_shape gives them."""
+    out = (C.c_int * 6)()
+    rc = lib().mplb_step_shape(nx, ny, nz, (C.c_int * 3)(*bc), precision, mode, VELOCITIES[velocity], int(study), rows,
+                               nsteps, out)
+    if rc:
+        raise MplbError(rc, "mplb_step_shape")
+    return _shape_dict(out)
 
 
 def mplb_required_bytes(nx, ny, nz, precision, mode):
@@ -357,6 +376,16 @@ def mplb_step_many(lattices, nsteps):
     """Advance several lattices together (batched launches).  Raises
     NonFiniteError naming the failed lattices when a non-finite check fails."""
     _many(lib().mplb_step_many, lattices, nsteps)
+
+
+def mplb_step_many_kinds(lattices, nsteps):
+    """The kernel (index into SHAPE_KINDS) that mplb_step_many first steps each lattice with."""
+    kinds = (C.c_int * max(1, len(lattices)))()
+    arr = (C.c_void_p * len(lattices))(*[lt.handle.value for lt in lattices])
+    rc = lib().mplb_step_many_kinds(arr, len(lattices), int(nsteps), kinds)
+    if rc:
+        raise MplbError(rc, lib().mplb_last_error(lattices[0].handle).decode() if lattices else "")
+    return list(kinds)[:len(lattices)]
 
 
 def mplb_step_many_noalloc(lattices, nsteps):

@@ -52,6 +52,15 @@ static thread_local int current = 0;
 static std::atomic<int> host_allocations{0}, host_live{0}, events_live{0};
 static std::atomic<int> copies{0};
 static int event_limit = 1 << 20;
+struct Launch {
+  unsigned blocks, threads;
+};
+static std::vector<Launch> launches;
+static thread_local struct {
+  dim3 grid, block;
+  size_t shared;
+  hipStream_t stream;
+} pushed;
 static const void *locked_from = nullptr, *locked_to = nullptr;  // page-locked memory of the caller
 static std::function<void()> during_host_malloc;
 static int device_of(hipStream_t s) { return s ? ((FakeStream*)s)->device : current; }
@@ -109,14 +118,25 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
 static char symbol[1 << 20];
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = symbol; return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t s) {
+  pushed = {grid, block, shared, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* s) {
+  *grid = pushed.grid; *block = pushed.block; *shared = pushed.shared; *s = pushed.stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
+  launches.push_back({grid.x, block.x});
+  return hipSuccess;
+}
 hipError_t hipGraphCreate(hipGraph_t*, unsigned) { return hipErrorNotSupported; }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 }
 
 // -------------------------------------------------------------- lattices
-static mplb_t* make(int nx, int ny, int nz, int precision, int mode, std::vector<char>& arena) {
+static mplb_t* make(int nx, int ny, int nz, int precision, int mode, std::vector<char>& arena, bool fill = true) {
   size_t need = 0;
   EXPECT(mplb_required_bytes(nx, ny, nz, precision, mode, &need) == MPLB_OK);
   arena.resize(need + 256);
@@ -132,7 +152,7 @@ static mplb_t* make(int nx, int ny, int nz, int precision, int mode, std::vector
   EXPECT(mplb_set_params(h, &p) == MPLB_OK);
   std::vector<double> phi((size_t)nx * ny * nz, 0.5);
   EXPECT(mplb_init(h, phi.data(), nullptr) == MPLB_OK);
-  for (size_t i = 0; i < need; ++i) base[i] = (char)(i * 2654435761u >> 24);  // what a checkpoint has to bring
+  for (size_t i = 0; i < need && fill; ++i) base[i] = (char)(i * 2654435761u >> 24);  // what a checkpoint has to bring
   return h;
 }
 
@@ -262,6 +282,75 @@ static void copy_without_events() {
   EXPECT(host_live == 0 && events_live == 0);
 }
 
+// The launches of mplb_step are those that mplb_step_shape names, and the kinds
+// that mplb_step_many_kinds names those of a batch's launches.
+static const unsigned kThreads[8] = {512, 1024, 512, 512, 256, 512, 512, 1024};  // by kind
+static void launches_are_the_shapes() {
+  std::vector<char> arena;
+  int seen[8] = {};
+  const struct {
+    int nx, ny, nz;
+  } boxes[] = {{9, 8, 7}, {64, 48, 40}, {48, 48, 64}, {96, 33, 34}, {256, 250, 1}, {600, 520, 1}, {64, 64, 280},
+               {176, 160, 160}, {64, 272, 260}, {1, 2200, 2100}};
+  for (const auto& b : boxes)
+    for (int prec = MPLB_F64; prec <= MPLB_F32_BF16; ++prec)
+      for (int mode : {MPLB_COUPLED, MPLB_CHE_ONLY, MPLB_COUPLED_Q19}) {
+        if (mode != MPLB_CHE_ONLY && (long)b.nx * b.ny * b.nz > 1500000) continue;  // (memory)
+        if (mode == MPLB_CHE_ONLY && prec == MPLB_F32_BF16) continue;
+        mplb_t* h = make(b.nx, b.ny, b.nz, prec, mode, arena, false);
+        EXPECT(mplb_set_check_interval(h, 0) == MPLB_OK);
+        for (int rows : {0, 8, 16})
+          for (int n : {1, 6}) {
+            const int bc[3] = {0, 0, 0};
+            int shape[6], one[6];
+            const int rc = mplb_step_shape(b.nx, b.ny, b.nz, bc, prec, mode, MPLB_VEL_ZERO, 0, rows, n, shape);
+            EXPECT((rc == MPLB_OK) == (mplb_force_tile_rows(h, rows) == MPLB_OK));
+            if (rc) continue;
+            launches.clear();
+            EXPECT(mplb_step(h, n) == MPLB_OK);
+            ++seen[shape[0]];
+            const bool pair = shape[0] == 7;
+            EXPECT((int)launches.size() == (pair ? n - 2 : n));  // six steps: two pairs and two steps
+            EXPECT(mplb_step_shape(b.nx, b.ny, b.nz, bc, prec, mode, MPLB_VEL_ZERO, 0, rows, 1, one) == MPLB_OK);
+            for (size_t i = 0; i < launches.size(); ++i) {
+              const int* s = pair && i >= 2 ? one : shape;
+              EXPECT(launches[i].blocks == (unsigned)s[5] && launches[i].threads == kThreads[s[0]]);
+            }
+          }
+        mplb_destroy(h);
+      }
+  for (int k : seen) EXPECT(k > 0);
+}
+
+static void batch_launches_are_the_kinds() {
+  const struct {
+    int prec, steps, nx, ny, nz, count, kind;
+  } batches[] = {{MPLB_F32, 3, 32, 32, 32, 4, 6},        // small as a whole
+                 {MPLB_F32, 1, 130, 128, 5, 9, 6},       // flat, but little idle
+                 {MPLB_F32, 9, 64, 64, 1, 20, 4},        // idle work of 0.98 M nodes,
+                 {MPLB_F32, 9, 64, 64, 1, 21, 0},        // 1.03 M
+                 {MPLB_F64, 9, 64, 64, 5, 22, 4},        // in FP64 0.43 M,
+                 {MPLB_F64, 9, 64, 64, 5, 23, 0},        // 0.45 M
+                 {MPLB_F32, 7, 96, 96, 40, 4, 0},        // 295 MB in few steps,
+                 {MPLB_F32, 8, 96, 96, 40, 4, 6},        // in enough for groups
+                 {MPLB_F32_F16, 31, 64, 64, 64, 8, 0},   // 243 MB with 16-bit populations
+                 {MPLB_F32_F16, 32, 64, 64, 64, 8, 6},
+                 {MPLB_F32_BF16, 32, 48, 48, 64, 13, 5}};
+  for (const auto& b : batches) {
+    std::vector<std::vector<char>> arena(b.count);
+    std::vector<mplb_t*> hs;
+    for (int i = 0; i < b.count; ++i) hs.push_back(make(b.nx, b.ny, b.nz, b.prec, MPLB_COUPLED, arena[i], false));
+    std::vector<int> kinds(b.count, -1);
+    EXPECT(mplb_step_many_kinds(hs.data(), b.count, b.steps, kinds.data()) == MPLB_OK);
+    for (int k : kinds) EXPECT(k == b.kind);
+    launches.clear();
+    EXPECT(mplb_step_many_noalloc(hs.data(), b.count, b.steps) == MPLB_OK);
+    EXPECT(!launches.empty());
+    for (const Launch& l : launches) EXPECT(l.threads == kThreads[b.kind]);
+    for (mplb_t* h : hs) mplb_destroy(h);
+  }
+}
+
 int main(int argc, char** argv) {
   const struct {
     const char* name;
@@ -271,6 +360,8 @@ int main(int argc, char** argv) {
                {"copy_from_another_device", copy_from_another_device},
                {"copy_without_events", copy_without_events},
                {"copy_to_page_locked", copy_to_page_locked},
+               {"launches_are_the_shapes", launches_are_the_shapes},
+               {"batch_launches_are_the_kinds", batch_launches_are_the_kinds},
                {"staging_of_short_lives", staging_of_short_lives},
                {"staging_is_allocated_unlocked", staging_is_allocated_unlocked}};
   for (const auto& c : cases)

@@ -30,7 +30,8 @@ def driver(tmp_path_factory):
 
 @pytest.mark.parametrize("case", ["copy_without_memory", "batch_without_memory", "copy_from_another_device",
                                   "copy_without_events", "copy_to_page_locked", "staging_of_short_lives",
-                                  "staging_is_allocated_unlocked"])
+                                  "staging_is_allocated_unlocked", "launches_are_the_shapes",
+                                  "batch_launches_are_the_kinds"])
 def test_host_path(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
