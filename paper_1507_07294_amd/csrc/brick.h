@@ -495,20 +495,28 @@ static_assert(brick_x(kBricksNarrow) * brick_y(kBricksNarrow) * 4 == brick_threa
                   brick_x(kBricksWide) * brick_y(kBricksWide) * 4 == brick_threads(kBricksWide),
               "one thread per node");
 
+// the coupled bricks that brick_kind picks
+constexpr bool coupled_bricks(int P, Bricks br) { return P != MPLB_F64 || br == kBricksNarrow; }
+
 template <int P, bool WALL, Bricks BR>
 hipError_t brick_impl3(int mode, const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur,
                        hipStream_t s) {
   constexpr int BX = brick_x(BR), BY = brick_y(BR), BZ = 4;
   const dim3 grid((unsigned)brick_blocks(G, BR)), block(brick_threads(BR));
-  if (mode == MPLB_CHE_ONLY)
+  if (mode == MPLB_CHE_ONLY) {
     hipLaunchKernelGGL((k_brick_che<P, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
-  else if (mode == MPLB_COUPLED_Q19)
-    hipLaunchKernelGGL((k_brick<P, 19, WALL, 0, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
-  else if (C.unit_rates)
-    hipLaunchKernelGGL((k_brick<P, 15, WALL, kVarUnit, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
-  else
-    hipLaunchKernelGGL((k_brick<P, 15, WALL, 0, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
-  return hipGetLastError();
+    return hipGetLastError();
+  }
+  if constexpr (coupled_bricks(P, BR)) {
+    if (mode == MPLB_COUPLED_Q19)
+      hipLaunchKernelGGL((k_brick<P, 19, WALL, 0, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
+    else if (C.unit_rates)
+      hipLaunchKernelGGL((k_brick<P, 15, WALL, kVarUnit, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
+    else
+      hipLaunchKernelGGL((k_brick<P, 15, WALL, 0, BX, BY, BZ>), grid, block, 0, s, G, C, B, cur);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int P, bool WALL>
@@ -531,11 +539,14 @@ hipError_t brick_impl(int mode, const Geo& G, const Coef<double>& Cd, const Bufs
 
 template <int P, bool WALL, int V>
 const void* brick_many3(Bricks br) {
-  switch (br) {
-    case kBricksWide: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksWide), brick_y(kBricksWide), 4>;
-    case kBricksMid: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksMid), brick_y(kBricksMid), 4>;
-    default: return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksNarrow), brick_y(kBricksNarrow), 4>;
+  if (br == kBricksNarrow)
+    return (const void*)k_brick_many<P, WALL, V, brick_x(kBricksNarrow), brick_y(kBricksNarrow), 4>;
+  if constexpr (coupled_bricks(P, kBricksWide)) {
+    return br == kBricksWide
+               ? (const void*)k_brick_many<P, WALL, V, brick_x(kBricksWide), brick_y(kBricksWide), 4>
+               : (const void*)k_brick_many<P, WALL, V, brick_x(kBricksMid), brick_y(kBricksMid), 4>;
   }
+  return nullptr;
 }
 template <int P>
 const void* brick_many2(bool wall, bool unit, Bricks br) {
@@ -610,17 +621,14 @@ Shape brick_shape(const Geo& G, Bricks br) {
   return Shape{kShapeBricks + (int)br - 1, bx, by, Tiling{(G.nx + bx - 1) / bx, (G.ny + by - 1) / by, 4, (G.nz + 3) / 4}};
 }
 
-size_t brick_bytes_limit(int P, int mode) {
-  return mode == MPLB_CHE_ONLY && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes;
-}
-
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
   if (C.stencil7 || C.forcing28) return kBricksNone;  // the study variants are marching kernels
   const long long n = (long long)G.nx * G.ny * G.nz;
   const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
   // (a CHE-only node with 16-bit populations: f_0 in 32 bits, six in 16, phi)
   const size_t bytes = mode == MPLB_CHE_ONLY && bits16 ? (size_t)n * 40 : fused_step_bytes(P, mode, n);
-  if (bytes > brick_bytes_limit(P, mode) || flat_work(G) > kFlatWork) return kBricksNone;
+  const size_t limit = mode == MPLB_CHE_ONLY && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes;
+  if (bytes > limit || flat_work(G) > kFlatWork) return kBricksNone;
   if (mode != MPLB_CHE_ONLY && bits16 && n > kBrickNodes16 && 10 * march_nodes(G) < 11 * n) return kBricksNone;
   return brick_kind(P, mode, n, 512LL * brick_blocks(G, kBricksMid), 512LL * brick_blocks(G, kBricksWide));
 }

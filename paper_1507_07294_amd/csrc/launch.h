@@ -26,7 +26,7 @@ hipError_t launch_che_pair(int P, const Geo& G, const Coef<double>& C, double ct
                            hipStream_t s);
 // The same step in three-dimensional bricks, one thread per node (brick.h),
 // for the lattices that step_bricks picks.
-enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksMid = 2, kBricksWide = 3, kBrickKinds = 4 };
+enum Bricks { kBricksNone = 0, kBricksNarrow = 1, kBricksMid = 2, kBricksWide = 3 };
 Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C);
 hipError_t launch_brick_step(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur, Bricks br,
                              hipStream_t s);
@@ -40,7 +40,6 @@ BatchUse batch_use(int P, const Geo& G);
 // a batch's flat lattices march.
 long long flat_work(const Geo& G);
 long long flat_work_limit(int P);
-size_t brick_bytes_limit(int P, int mode);
 Bricks batch_bricks(int P, long long nodes, long long mid, long long wide);
 const void* brick_many_kernel(int P, bool wall, bool unit, Bricks br);
 constexpr int brick_threads(Bricks br) { return br == kBricksNarrow ? 256 : 512; }

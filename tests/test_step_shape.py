@@ -101,3 +101,18 @@ def test_the_boxes_of_the_bitwise_tests():
         assert all(k >= NARROW for k in [kind(s, p, mode, 5, bc=bc) for s, bc in bricks.BOXES])
     for p, boxes in pairs.BOXES.items():
         assert [kind(s, p, CHE, 4) for s in boxes] == [PAIR] * len(boxes), p
+
+
+def test_fp64_coupled_bricks_are_built_in_the_one_size_they_step_in():
+    """FP64 coupled lattices take 16 x 4 x 4 bricks at every size, so the library
+    carries no other coupled FP64 brick kernel."""
+    import re
+    import subprocess
+    out = subprocess.run(["nm", "-C", mplb.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    built = {(m[1], m[2]) for m in re.finditer(r"__device_stub__(k_brick|k_brick_many)<0, [^>]*?(\d+, \d+, \d+)>", out)}
+    assert built == {("k_brick", "16, 4, 4"), ("k_brick_many", "16, 4, 4")}
+    rng = np.random.default_rng(11)
+    for _ in range(500):
+        dims = tuple(int(v) for v in np.exp(rng.uniform(0, np.log(100), 3)).astype(int) + 1)
+        for mode in (COUPLED, Q19):
+            assert kind(dims, "f64", mode) in (0, NARROW)
