@@ -625,8 +625,7 @@ Bricks step_bricks(int P, int mode, const Geo& G, const Coef<double>& C) {
   if (C.stencil7 || C.forcing28) return kBricksNone;  // the study variants are marching kernels
   const long long n = (long long)G.nx * G.ny * G.nz;
   const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;
-  // (a CHE-only node with 16-bit populations: f_0 in 32 bits, six in 16, phi)
-  const size_t bytes = mode == MPLB_CHE_ONLY && bits16 ? (size_t)n * 40 : fused_step_bytes(P, mode, n);
+  const size_t bytes = fused_step_bytes(P, mode, n);
   const size_t limit = mode == MPLB_CHE_ONLY && P == MPLB_F64 ? kBrickBytesCheF64 : kBrickBytes;
   if (bytes > limit || flat_work(G) > kFlatWork) return kBricksNone;
   if (mode != MPLB_CHE_ONLY && bits16 && n > kBrickNodes16 && 10 * march_nodes(G) < 11 * n) return kBricksNone;

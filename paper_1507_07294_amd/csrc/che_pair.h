@@ -366,7 +366,7 @@ hipError_t pair_impl2(const Geo& G, const Coef<double>& Cd, double ct_next, cons
 
 template <int P>
 hipError_t pair_impl(const Geo& G, const Coef<double>& C, double ct_next, const Bufs& B, int cur, hipStream_t s) {
-  if (fused_step_bytes(P, MPLB_CHE_ONLY, G.N) > fused_stream_threshold())
+  if (streaming_stores(P, MPLB_CHE_ONLY, fused_step_bytes(P, MPLB_CHE_ONLY, G.N)))
     return pair_impl2<P, true>(G, C, ct_next, B, cur, s);
   return pair_impl2<P, false>(G, C, ct_next, B, cur, s);
 }

@@ -765,8 +765,12 @@ Tiling make_tiling(const Geo& G, int TY, int min_lz, int target = 0, int TW = kT
 
 // Streaming stores pay once a step moves much more than the 256 MB
 // last-level cache holds (measured: about 3 % faster at 256 x 256 x 1024,
-// 18 % slower for a 128^3 CHE-only box that stays cache-resident).
-constexpr size_t kStreamBytes = (size_t)512 << 20;
+// 18 % slower for a 128^3 CHE-only box that stays cache-resident).  A CHE-only
+// step with 16-bit populations gains from fewer bytes on, us per step streaming /
+// not: pairs on 208^3 (360 MB) 105 / 110, 224^3 110 / 112, 512 x 300 x 70 (430 MB)
+// 121 / 126, 232^3 (500 MB) 128 / 127; single steps 126 / 124, 130 / 132, 121 / 126,
+// but 175 / 156 on 232^3.
+constexpr size_t kStreamBytes = (size_t)512 << 20, kStreamBytesChe16 = kStreamBytes / 8 * 5;
 
 // One coupled step with TY-row tiles.
 template <int P, int TY, bool XYWALL, bool NT, int V>
@@ -939,7 +943,7 @@ hipError_t fused_impl3(int mode, const Geo& G, const Coef<typename Prec<P>::T>& 
 template <int P, bool XYWALL>
 hipError_t fused_impl2(int mode, const Geo& G, const Coef<typename Prec<P>::T>& C, const Bufs& B, int cur,
                        hipStream_t s, int rows) {
-  if (fused_step_bytes(P, mode, G.N) > kStreamBytes)
+  if (streaming_stores(P, mode, fused_step_bytes(P, mode, G.N)))
     return fused_impl3<P, XYWALL, true>(mode, G, C, B, cur, s, rows);
   return fused_impl3<P, XYWALL, false>(mode, G, C, B, cur, s, rows);
 }
@@ -1091,13 +1095,17 @@ hipError_t build_fused_many_graph(int P, const BatchForm& form, const void* dtab
   return hipSuccess;
 }
 
-size_t fused_stream_threshold() { return kStreamBytes; }
+bool streaming_stores(int P, int mode, size_t bytes) {
+  const bool che16 = mode == MPLB_CHE_ONLY && (P == MPLB_F32_F16 || P == MPLB_F32_BF16);
+  return bytes > (che16 ? kStreamBytesChe16 : kStreamBytes);
+}
 
 size_t fused_step_bytes(int P, int mode, long long N) {
-  // populations and history read and written once per update
+  // populations and history read and written once per update (CHE-only with
+  // 16-bit populations: f_0 in 32 bits, six in 16, phi in 32)
   size_t per = mode == MPLB_COUPLED       ? (P == MPLB_F64 ? 400 : (P == MPLB_F32 ? 200 : 116))
                : mode == MPLB_COUPLED_Q19 ? (P == MPLB_F64 ? 464 : (P == MPLB_F32 ? 232 : 132))
-                                          : (P == MPLB_F64 ? 128 : 64);
+                                          : (P == MPLB_F64 ? 128 : (P == MPLB_F32 ? 64 : 40));
   return per * (size_t)N;
 }
 

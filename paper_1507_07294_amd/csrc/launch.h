@@ -60,8 +60,8 @@ size_t fused_batch_item_bytes(int P);
 int fused_batch_fill(int P, void* table, int i, const Geo& G, const Coef<double>& C, const Bufs& B, int cur0,
                      int block0, Bricks br);
 // bricks: kBricksNone for the march; wall: some lattice has a wall on the x or
-// y axis (bricks: on any axis); nt: streaming stores (march), for batches whose
-// step moves more than kStreamBytes, see fused_step_bytes; unit: every item has
+// y axis (bricks: on any axis); nt: streaming stores (march), for batches of
+// streaming_stores; unit: every item has
 // S^g = 1 off the stress moments, the form its lattice uses alone
 struct BatchForm {
   Bricks bricks;
@@ -85,8 +85,8 @@ size_t noalloc_table_bytes();
 // algorithmic bytes one step of an N-node lattice moves (populations and
 // history read and written once)
 size_t fused_step_bytes(int P, int mode, long long N);
-// step traffic above which the step kernels use streaming stores
-size_t fused_stream_threshold();
+// whether a step that moves `bytes` uses streaming stores
+bool streaming_stores(int P, int mode, size_t bytes);
 // field (MPLB_PHI..MPLB_P) at the current level into B.out (double)
 hipError_t launch_macro(int P, int mode, const Geo& G, const Coef<double>& C, const Bufs& B, int cur,
                         int field, hipStream_t s);

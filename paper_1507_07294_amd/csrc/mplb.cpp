@@ -809,7 +809,7 @@ static int plan_batch(mplb_t* const* hs, int count, int nsteps, bool unit, Batch
   size_t march_bytes = 0;
   for (int i = 0; i < count; ++i)
     if (hs[i]->batch_group == march) march_bytes += bytes_of(i);
-  if (march >= 0) out[march].form.nt = march_bytes > fused_stream_threshold();
+  if (march >= 0) out[march].form.nt = streaming_stores(P, MPLB_COUPLED, march_bytes);
   int first = 0;
   for (int g = 0; g < ng; ++g) {
     out[g].alone = split && out[g].count == 1;
