@@ -28,7 +28,7 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
 # history, each read and written once), per storage mode
 ALGO_BYTES = {"f64": 400, "f32": 200, "f16": 116, "bf16": 116}
 Q19_ALGO_BYTES = {"f64": 464, "f32": 232, "f16": 132, "bf16": 132}  # D3Q19: 19 g instead of 15
-CHE_ALGO_BYTES = {"f64": 2 * 8 * 8, "f32": 2 * 4 * 8}  # 7 populations + phi of the previous level
+CHE_ALGO_BYTES = {"f64": 2 * 8 * 8, "f32": 2 * 4 * 8, "f16": 2 * (4 * 2 + 6 * 2)}  # 7 populations + phi of the previous level
 
 
 def parse():
@@ -105,6 +105,40 @@ def time_lattice(lt, steps, warmup):
     stages = lt.time_stages(max(1, min(steps, 50)))
     n_st = max(1, min(steps, 50))
     return dt, [v / n_st for v in stages]
+
+
+# kernels of CHE-only steps by the kind that mplb_step_shape gives
+CHE_KERNELS = {2: "k_fused_che", 3: "k_fused_che2", 4: "k_brick_che", 5: "k_brick_che", 6: "k_brick_che",
+               7: "k_che_pair"}
+
+
+def che_record(lt, w, name, precision, steps, warmup):
+    """Rates of a CHE-only lattice, workload `name`.  `kernel` is the one that the
+    timed steps start with.  Where that is a pair (two steps per launch) the
+    `traffic` is that of two steps, and the algorithmic rate is no rate of HBM:
+    the populations between the two steps stay on the chip.  The k_ figures
+    time single steps, and k_kernel is the kernel that runs those."""
+    from paper_1507_07294_amd import mplb
+    kinds = [mplb.mplb_step_shape(*w.shape, w.bc, lt.precision, lt.mode, w.velocity["kind"], nsteps=n)["kind"]
+             for n in (steps, 1)]
+    kernel, single = (CHE_KERNELS[k] for k in kinds)
+    dt, st = time_lattice(lt, steps, warmup)
+    algo = CHE_ALGO_BYTES[precision]
+    per_launch = 2 if kernel == "k_che_pair" else 1
+    traffic = measured_traffic(kernel, name, precision)
+    rec = {"workload": name, "kernel": kernel, "steps_per_launch": per_launch,
+           "MLUPS": round(w.nodes * steps / dt / 1e6, 1), "ms_per_step": round(dt / steps * 1e3, 4),
+           "algorithmic_bytes_per_lup": algo,
+           "algorithmic_GBps": round(algo * w.nodes / (dt / steps) / 1e9, 1),
+           "traffic": traffic,
+           "k_kernel": single, "k_step_ms": round(st[2], 4),
+           "k_achieved_GBps": round(algo * w.nodes / (st[2] * 1e-3) / 1e9, 1),
+           "k_frac": round(algo * w.nodes / (st[2] * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)}
+    if per_launch == 1:
+        rec["hbm_frac_step"] = round(algo * w.nodes / (dt / steps) / 1e9 / HBM_PEAK_GBPS, 4)
+    if traffic is not None:  # what the counters saw, at the timed steps' rate
+        rec["traffic_frac_step"] = round(traffic / per_launch / (dt / steps) / 1e9 / HBM_PEAK_GBPS, 4)
+    return rec
 
 
 def cpu_baseline(W, target_s=12.0, single_s=6.0):
@@ -243,44 +277,17 @@ def main():
 
     if not args.no_che:
         # the interface-tracking step on the 128^3 box of the paper's tests
-        # (its 126 MB stay in the last-level cache; bricks) and on 256^3, whose
-        # steps run in pairs (k_che_pair; its traffic is that of two steps).
-        # k_step_ms and what follows from it time single steps, on 256^3 the
-        # marching kernel's 1.07 GB per step.
-        for n, key in ((128, "che_only"), (256, "che_only_256")):
+        # (its 126 MB stay in the last-level cache) and on 256^3, in FP32 and
+        # with 16-bit storage of f_1..f_6 (f_0 and phi of the previous level
+        # FP32: 40 B per update)
+        for n, prec, key in ((128, "f32", "che_only"), (256, "f32", "che_only_256"), (256, "f16", "che_only_256_f16")):
             wc = wl.deformation_flow(n=n)
-            print(f"[bench] deformation_flow {n}^3 f32 (CHE only)", file=sys.stderr, flush=True)
-            lt = mplb.from_workload(wc, "f32")
-            steps = args.steps
-            dtc, stc = time_lattice(lt, steps, args.warmup)
-            kc = CHE_ALGO_BYTES["f32"] * wc.nodes / (stc[2] * 1e-3) / 1e9
-            result[key] = {"workload": f"deformation_flow_{n}^3", "MLUPS": round(wc.nodes * steps / dtc / 1e6, 1),
-                           "ms_per_step": round(dtc / steps * 1e3, 4),
-                           "algorithmic_bytes_per_lup": CHE_ALGO_BYTES["f32"],
-                           "hbm_frac_step": round(CHE_ALGO_BYTES["f32"] * wc.nodes / (dtc / steps) / 1e9
-                                                  / HBM_PEAK_GBPS, 4),
-                           "k_step_ms": round(stc[2], 4), "k_achieved_GBps": round(kc, 1),
-                           "k_frac": round(kc / HBM_PEAK_GBPS, 4),
-                           "kernel": "k_che_pair" if n >= 256 else "k_brick_che",
-                           "traffic": measured_traffic("k_che_pair" if n >= 256 else "k_brick_che",
-                                                       f"deformation_flow_{n}^3", "f32")}
+            print(f"[bench] deformation_flow {n}^3 {prec} (CHE only)", file=sys.stderr, flush=True)
+            lt = mplb.from_workload(wc, prec)
+            result[key] = che_record(lt, wc, f"deformation_flow_{n}^3", prec, args.steps, args.warmup)
             lt.destroy()
             del lt
             torch.cuda.empty_cache()
-        # the same 256^3 step with 16-bit storage of f_1..f_6 (f_0 and phi of
-        # the previous level FP32): 40 B per update
-        wc = wl.deformation_flow(n=256)
-        lt = mplb.from_workload(wc, "f16")
-        dtc, stc = time_lattice(lt, args.steps, args.warmup)
-        result["che_only_256_f16"] = {"workload": "deformation_flow_256^3", "kernel": "k_che_pair",
-                                      "MLUPS": round(wc.nodes * args.steps / dtc / 1e6, 1),
-                                      "ms_per_step": round(dtc / args.steps * 1e3, 4), "algorithmic_bytes_per_lup": 40,
-                                      "k_step_ms": round(stc[2], 4),
-                                      "k_frac": round(40 * wc.nodes / (stc[2] * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
-                                      "traffic": measured_traffic("k_che_pair", "deformation_flow_256^3", "f16")}
-        lt.destroy()
-        del lt
-        torch.cuda.empty_cache()
 
     if args.copy_probe:
         # bandwidth reference: the library's 16-byte copies (plain, streaming
