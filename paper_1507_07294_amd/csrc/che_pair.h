@@ -340,6 +340,8 @@ PairPlan pair_plan(const Geo& G, int TY) {
   long long best = 0;
   for (int want = 1; want == 1 || (G.nz + want - 1) / want >= kPairMinLz; ++want) {
     const int lz = (G.nz + want - 1) / want, nseg = (G.nz + lz - 1) / lz;
+    // shorter segments cost at least (lz + 6) / lz of their planes' even share
+    if (best && (double)cols * G.nz * (lz + 6) >= (double)best * lz * kPairCUs) break;
     if (G.nz - (nseg - 1) * lz < 2) continue;
     const long long cost = (cols * nseg + kPairCUs - 1) / kPairCUs * (lz + 6);
     if (best && cost >= best) continue;

@@ -57,6 +57,34 @@ def test_pairs():
     assert kind((1000, 1000, 6), "f32", CHE, 4) == 3 and kind((200, 200, 200), "f16", CHE, 4) == 3
 
 
+def test_the_split_of_a_pair():
+    """The cheapest of all splits, found without trying all of a long column's."""
+    import time
+    rng = np.random.default_rng(5)
+    checked = 0
+    while checked < 150:
+        dims = tuple(int(v) for v in np.exp(rng.uniform(0, np.log(3000), 3)).astype(int) + 1)
+        if not 5e6 < np.prod(dims, dtype=float) < 5e8:
+            continue
+        s = mplb.mplb_step_shape(*dims, (0, 0, 0), P["f32"], CHE, nsteps=4)
+        if s["kind"] != PAIR:
+            continue
+        nz, cols, best = dims[2], -(-dims[0] // 64) * -(-dims[1] // 16), None
+        for want in range(1, max(1, nz // 15) + 1):
+            lz = -(-nz // want)
+            nseg = -(-nz // lz)
+            if (want > 1 and lz < 16) or nz - (nseg - 1) * lz < 2:
+                continue
+            cost = -(-cols * nseg // 256) * (lz + 6)
+            if best is None or cost < best[0]:
+                best = (cost, lz, nseg)
+        assert (s["lz"], s["segments"]) == best[1:], (dims, s, best)
+        checked += 1
+    t0 = time.perf_counter()
+    kind((1, 1, 1 << 30), "f32", CHE, 4), kind((1, 16, 60000000), "f32", CHE, 4)
+    assert time.perf_counter() - t0 < 0.15  # 0.4 s with every split
+
+
 def test_a_march_is_the_one_that_the_launch_shape_names():
     rng = np.random.default_rng(7)
     seen = set()
