@@ -17,8 +17,9 @@
 // 22.4, D3Q19 64 x 64 x 256 FP32 56.2 / 45.7 (5.3 TB/s), CHE-only 64^3 FP32
 // 14.1 / 6.3, 128^3 29.4 / 27.6 (4.9 TB/s).  What is left on the larger of these
 // is the traffic of the last-level cache (a copy of their size moves 6-7 TB/s)
-// and the vector-memory instructions of the halo pulls (4.0-4.5 times the
-// brick's own nodes in the coupled step, 2.4-2.5 in the CHE-only one).
+// and the vector-memory instructions of the halo pulls: halo nodes per node of
+// the brick (16 x 4 x 4, 16 x 8 x 4, 32 x 4 x 4) 4.0, 2.75, 3.5 in the coupled
+// step, 1.53, 1.11, 1.39 in the CHE-only one.
 #pragma once
 
 #include "common.h"
@@ -577,9 +578,13 @@ constexpr long long kBrickNodes16 = 1200000;
 // 32.2 / 35.0 mid / 39.4 wide).  Otherwise wide ones, whose rows are a whole
 // cache line, where they cover at most 1.2 times the nodes that mid ones do
 // (1.1 with 16-bit populations), else mid ones.  Mid against wide: FP32
-// 64 x 64 x 256 40.1 / 36.2, 72^3 (1.2) 21.5 / 19.3, 48 x 48 x 192 (1.33)
-// 20.7 / 21.4; FP16 70 x 77 x 69 (1.2) 16.9 / 18.7, 100^3 (1.14) 34.9 / 35.3;
-// CHE-only FP32 128^3 29.3 / 27.1, FP64 64^3 9.5 / 9.0.
+// 64 x 64 x 256 40.1 / 36.2, 72^3 (1.2) 21.2 / 18.4, 70 x 77 x 69 (1.2) 21.6 /
+// 20.5, 48 x 48 x 192 (1.33) 20.7 / 21.4; FP16 128 x 100 x 80 (0.96) 32.8 / 29.6,
+// 100^3 (1.10) 33.2 / 32.0, 112 x 112 x 84 (1.14) 33.0 / 32.5, 70 x 77 x 69 (1.2)
+// 17.3 / 17.9, 80^3 (1.2) 18.1 / 18.7; CHE-only FP32 128^3 29.3 / 27.1, FP64
+// 64^3 9.5 / 9.0.  These are periodic boxes at the paper's rates; with walls on
+// every axis and other rates mid ones gain 3-15 % against wide ones (FP32 70 x
+// 77 x 69 21.1 / 21.8, FP16 100^3 32.2 / 36.0), which the rule does not look at.
 Bricks brick_kind(int P, int mode, long long nodes, long long mid, long long wide) {
   if (nodes < 100000 || (mode != MPLB_CHE_ONLY && P == MPLB_F64)) return kBricksNarrow;
   const bool bits16 = P == MPLB_F32_F16 || P == MPLB_F32_BF16;

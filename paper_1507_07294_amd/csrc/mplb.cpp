@@ -150,8 +150,8 @@ struct Staging {
 };
 // Up to kPool of them live, whatever their device; a copy that finds none free
 // takes the runtime's path.  They are freed with the last lattice, so a program
-// that holds one lattice at a time has one allocated for each, which takes about
-// 40 us with the free.  Smaller copies than kStagedCopy, which the runtime makes
+// that holds one lattice at a time has one allocated for each, which takes some
+// 50 us with the free.  Smaller copies than kStagedCopy, which the runtime makes
 // as fast, do without.  Life of a lattice that is read once, three times, us,
 // runtime / staging with its allocation / without: 0.88 MB 69, 190 / 117, 257 / 73,
 // 214; 1.4 MB 108, 315 / 138, 338 / 100, 291; 1.7 MB 145, 426 / 160, 365 / 105, 311;
@@ -229,9 +229,10 @@ static Staging* take_staging(int dev) {
 }
 
 // Copies from which several threads copy the chunks out, and their number (a
-// divisor of kSlots, so that a slot stays with one thread).  A field of 2.1 MB
-// takes 146 us alone and 163 in the threads' chunks, 7.1 MB 373 and 337, 134 MB
-// 10 400 and 4 150 (two threads 6 230, eight 4 165).
+// divisor of kSlots, so that a slot stays with one thread).  A read of 2.1 MB
+// takes 121 us on one thread and 137 on four, 3.5 MB 192 and 205, 5.8 MB 267 and
+// 260, 7.1 MB 321 and 290, 134 MB into fresh memory 10 400 and 4 100 (two threads
+// 6 230, eight 4 165).
 constexpr size_t kThreadedCopy = (size_t)6 << 20;
 constexpr int kCopyThreads = 4;
 static_assert(Staging::kSlots % kCopyThreads == 0, "each slot belongs to one thread");
