@@ -136,7 +136,7 @@ def che_record(lt, w, name, precision, steps, warmup):
            "k_frac": round(algo * w.nodes / (st[2] * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)}
     if per_launch == 1:
         rec["hbm_frac_step"] = round(algo * w.nodes / (dt / steps) / 1e9 / HBM_PEAK_GBPS, 4)
-    if traffic is not None:  # what the counters saw, at the timed steps' rate
+    if traffic is not None:  # what the counters saw beyond L2 (HBM or the last-level cache), at the timed steps' rate
         rec["traffic_frac_step"] = round(traffic / per_launch / (dt / steps) / 1e9 / HBM_PEAK_GBPS, 4)
     return rec
 
